@@ -325,28 +325,26 @@ int32_t hapmoe_stage_dp_1f1b(const hapmoe_problem *p, const void *d_image,
  *   T = sum_i c_i + sum_{i <= s} ceil(c_i / 3) + max(0, B - s - 1) * max_i c_i,
  * s the first (1-based) stage of largest cost, minimised over every partition
  * that passes the three prunings (stage costs, recomputation and memory as in
- * hapmoe_stage_dp).  For every distinct stage cost t, ascending from the least
- * possible largest stage (the thresholds below it admit no partition), a DP over
- * (stage, end layer, bottleneck placed yet) gives the least T with largest
- * stage exactly t; the sweep stops once F_inf + ceil(t / 3) +
- * max(0, B - PP - 1) t, F_inf the least stage sum, reaches the best T.  Ties:
- * least T, then the lower largest stage, then the lexicographically smallest
- * (b_PP-1, ..., b_1) of the stage end layers.  For each candidate of
- * [first, first + count) writes d_res[i - first]: objective = T + C, stage_sum
- * and t_max of the chosen partition, its recomputation mask and stage lengths.
- * One workgroup per (configuration, ordering) key, lane j holding the key's
- * j-th candidate, the deepest pipelines first.  Its stage-cost table holds, for
- * every stage, end layer b of the stage's band (the end layers its windows
- * allow) and split point of its window, an 8-byte cost c (kept as
- * c + ceil(c / 3)) and a 1-byte recomputation flag (the flags rounded up to 16
- * bytes), plus 16 bytes of DP state for every (stage, b).
- * Launches in tiers of LDS a workgroup: every candidate with 24 KB, then those
- * whose table did not fit (over 22,784 bytes) with 40, 80 and 160 KB; a
- * candidate whose table exceeds 162,048 bytes gets HAPMOE_STATUS_OVERFLOW.  The candidates of a (configuration, ordering) key
- * with B >= PP + 1 share one sweep (their latencies at a threshold t differ by
- * (B - B') t); d_stats (may be NULL): thresholds swept for the candidate, and
- * DP relaxations counted on the first candidate of each shared sweep (columns
- * 2, 3 zero).  No workspace.  Not for
+ * hapmoe_stage_dp).  Branch and bound over ranges of the largest stage cost t: a
+ * DP pass over (stage, end layer, bottleneck placed yet) bounds T from below for
+ * every t of a range and is exact for a single t; a range whose path is no
+ * partition with that largest stage splits, and is dropped once it cannot beat
+ * the best T found.  Ties: least T, then the lower largest stage, then the
+ * lexicographically smallest (b_PP-1, ..., b_1) of the stage end layers.  For
+ * each candidate of [first, first + count) writes d_res[i - first]: objective =
+ * T + C, stage_sum and t_max of the chosen partition, its recomputation mask and
+ * stage lengths.  One workgroup per (configuration, ordering) key, lane j holding
+ * the key's j-th candidate, the deepest pipelines first.  A key's table is
+ * counted at 9 bytes for every (stage, end layer b of the stage's band, split
+ * point of its window) plus 16 bytes for every (stage, b), the one-byte parts
+ * rounded up to 16 bytes; a candidate whose table exceeds 162,048 bytes gets
+ * HAPMOE_STATUS_OVERFLOW.  Launches in tiers of LDS a workgroup, 20 to 40 KB
+ * (the size the deepest pipelines are expected to take), then 40, 80 and 160 KB
+ * for the keys that did not fit.  The candidates of a (configuration, ordering)
+ * key with B >= PP + 1 share one search (their latencies at a t differ by
+ * (B - B') t); d_stats (may be NULL): passes over ranges of the candidate's
+ * search, and DP relaxations counted on the first candidate of each shared one
+ * (columns 2, 3 zero).  No workspace.  Not for
  * stage_types = 2 or 3 (HAPMOE_E_INVAL); ranges and errors as hapmoe_stage_dp.
  * Asynchronous. */
 int32_t hapmoe_stage_dp_latency(const hapmoe_problem *p, const void *d_image,

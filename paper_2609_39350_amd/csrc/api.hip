@@ -536,8 +536,11 @@ int32_t hapmoe_stage_dp_latency(const hapmoe_problem *p, const void *d_image, co
                                          p->model.n_layers);
     if (tables_bytes < L.total) return HAPMOE_E_WORKSPACE;
     if (const int e = check_arch()) return e;
+    std::vector<int32_t> depths;   // configurations are PP-ascending
+    for (const auto &cf : S.cfg)
+        if (depths.empty() || depths.back() != cf[0]) depths.push_back(cf[0]);
     if (launch_latency_dp(d_image, d_cand, p->space.n_micro, L, d_tables, first, count, d_res, d_stats,
-                          (hipStream_t)stream) != hipSuccess)
+                          latency_dp_lds(*p, depths), (hipStream_t)stream) != hipSuccess)
         return HAPMOE_E_HIP;
     return HAPMOE_OK;
 }

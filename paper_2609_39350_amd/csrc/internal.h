@@ -135,10 +135,12 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
                            hapmoe_dp_result *d_res, int32_t *d_stats, void *d_ws, const int32_t *micro,
                            bool exact, hipStream_t s);
 int64_t stage_dp_ws_bytes();
-// the least 1F1B latency over every partition: one workgroup per candidate
+// the least 1F1B latency over every partition: one workgroup per key; lds_hint:
+// what latency_dp_lds expects a workgroup to need for the pipeline depths of the space
+int latency_dp_lds(const hapmoe_problem &p, const std::vector<int32_t> &depths);
 hipError_t launch_latency_dp(const void *d_image, const hapmoe_candidate *d_cand, int n_micro,
                              const TablesLayout &L, const void *d_tables, int64_t first, int64_t count,
-                             hapmoe_dp_result *d_res, int32_t *d_stats, hipStream_t stream);
+                             hapmoe_dp_result *d_res, int32_t *d_stats, int lds_hint, hipStream_t stream);
 // section clocks of the stage-DP kernel (libraries built with HAPMOE_SECTION_CLOCKS)
 enum {
     kClockSetup, kClockScan, kClockRelax, kClockTrace, kClockControl, kClockTotal,

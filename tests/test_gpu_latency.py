@@ -214,3 +214,38 @@ def test_latency_oversized_table_reports_overflow(torch):
     assert set(depth[over]) == {4} and set(depth[second]) == {2}
     assert np.array_equal(res["status"] == 2, over)
     assert compare(p, res, np.nonzero(~over)[0]) > 0
+
+
+def near_ties(problem):
+    """Every layer a copy of layer 0: equal costs and equal latencies everywhere."""
+    for d, f in (("model", "params_dense"), ("model", "params_expert"), ("model", "act_bytes"),
+                 ("model", "is_moe"), ("cluster", "t_dense"), ("cluster", "t_ffn")):
+        problem[d][f][:] = problem[d][f][..., :1]
+    problem["model"]["expert_tokens"][:] = problem["model"]["expert_tokens"][:1]
+    return problem
+
+
+@pytest.mark.parametrize("n_layers,max_pp,scale,ties", [
+    (13, 8, 1, False),        # 32-bit weights
+    (13, 8, 1500, False),     # both widths: shallow pipelines pass 2^31, deep ones stay below
+    (17, 8, 10**6, False),    # 64-bit weights everywhere
+    (16, 8, 1, True), (12, 4, 10**5, True),
+    (30, 4, 1, False),        # bands of more than 24 end layers: two slots a wave
+])
+def test_latency_ranges(torch, n_layers, max_pp, scale, ties):
+    """The range search against the oracle's threshold sweep: shared searches of
+    many micro-batch counts (a duplicate among them), counts below and above the
+    depth, weights on both sides of 2^31, ties everywhere, wide bands."""
+    p = workloads.random_tiny(300 + n_layers, n_layers=n_layers, n_types=2, max_pp=max_pp,
+                              micro=[1, 2, 3, 4, 5, 6, 9, 9, 17, 40, 64, 1000])
+    p["params"]["prune_window"] = 0
+    p["params"]["prune_hetero"] = 0
+    p["cluster"]["count"][:] = 8
+    p["cluster"]["mem_bytes"] = p["cluster"]["mem_bytes"] * 10
+    p["cluster"]["t_dense"] = p["cluster"]["t_dense"] * scale
+    p["cluster"]["t_ffn"] = p["cluster"]["t_ffn"] * scale
+    if ties:
+        p = near_ties(p)
+    pl, res = run_latency(p)
+    idx = np.linspace(0, pl.n - 1, min(pl.n, 1500)).astype(np.int64)
+    assert compare(p, res, sorted(set(int(i) for i in idx))) > 0
