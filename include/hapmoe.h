@@ -397,8 +397,9 @@ int32_t hapmoe_stage_dp_types_1f1b(const hapmoe_problem *p, const void *d_image,
                                    void *d_ws, int64_t ws_bytes, void *stream);
 
 /* Workspace of hapmoe_stage_dp_widths for a launch over `count` candidates: the
- * work-queue counter and one slice of back-trace pointers per workgroup (at
- * most 1024; the DP values themselves live in the workgroup's LDS).
+ * work-queue counters, a list of the keys whose DP state exceeds the first
+ * launch's LDS (4 bytes a candidate) and a slice per workgroup of the launch that
+ * takes those keys (at most 256).
  * HAPMOE_E_INVAL unless stage_types = 3. */
 int32_t hapmoe_stage_dp_widths_ws_bytes(const hapmoe_problem *p, int64_t count, int64_t *bytes);
 
@@ -423,7 +424,8 @@ int32_t hapmoe_stage_dp_widths_ws_bytes(const hapmoe_problem *p, int64_t count, 
  * stage and d_widths[32 * (0 .. count)] each w_i (0 past PP and for infeasible
  * candidates).  d_stats (may be NULL): passes of the candidate's sweep and its
  * relaxations, counted on the first candidate of the key that shares the sweep
- * (those with equal min(B, PP) share every pass; columns 2, 3 zero).  The tables must come from
+ * (those with equal min(B, PP) share every pass, the first of which finds the
+ * least possible largest stage; columns 2, 3 zero).  The tables must come from
  * hapmoe_eval_cost_tables on the same problem (which adds the width tables).
  * d_ws (hapmoe_stage_dp_widths_ws_bytes for count) is the kernel's: calls that
  * may overlap need their own.  Asynchronous. */

@@ -630,8 +630,8 @@ int32_t hapmoe_stage_dp_widths(const hapmoe_problem *p, const void *d_image, con
     if (tables_bytes < L.total || ws_bytes < width_dp_ws_bytes(p->model.n_layers, S.ppmax, count))
         return HAPMOE_E_WORKSPACE;
     if (const int e = check_arch()) return e;
-    if (launch_width_dp(d_image, d_cand, p->model.n_layers, S.ppmax, L, d_tables, first, count, d_res, d_types, d_widths,
-                        d_stats, d_ws, (hipStream_t)stream) != hipSuccess)
+    if (launch_width_dp(*p, d_image, d_cand, S.ppmax, L, d_tables, first, count, d_res, d_types, d_widths, d_stats,
+                        d_ws, (hipStream_t)stream) != hipSuccess)
         return HAPMOE_E_HIP;
     return HAPMOE_OK;
 }

@@ -150,3 +150,69 @@ def test_config3_launch_and_shallow_sample(torch):
     idx = sorted(set(shallow[:: max(1, len(shallow) // 120)].tolist()))
     from tests.test_gpu_parity import oracle_many
     assert compare(p, pl, idx, ref=oracle_many(p, idx, pool=True)) > 0
+
+
+def _numpy_sweep(cost, micro):
+    """Least sum + (B-1) max over the width sequences and partitions on an explicit cost
+    tensor [pp][2pp+1][3][n+1][n+1]: (objective, sum, largest stage), the least largest
+    stage on ties, by passes at descending thresholds from infinity.  A pass keeps the
+    least (sum, largest stage) of every state, which a longer path keeps in order."""
+    big = np.int64(1) << 60
+    pp, units, _, w1, _ = cost.shape
+    cost = np.minimum(cost, big)
+
+    def least_sum(t):
+        f, m = np.full((units, w1), big), np.full((units, w1), big)
+        f[0, 0] = m[0, 0] = 0
+        for s in range(pp):
+            g, h = np.full((units, w1), big), np.full((units, w1), big)
+            for w in (1, 2, 3):
+                for u in range(units - w):
+                    if f[u].min() == big:
+                        continue
+                    c = cost[s, u, w - 1]
+                    v = np.where(c <= t, np.minimum(f[u][:, None] + c, big), big)
+                    least = v.min(axis=0)
+                    mx = np.where(v == least, np.maximum(m[u][:, None], c), big).min(axis=0)
+                    better = (least < g[u + w]) | ((least == g[u + w]) & (mx < h[u + w]))
+                    g[u + w], h[u + w] = np.where(better, least, g[u + w]), np.where(better, mx, h[u + w])
+            f, m = g, h
+        return int(f[units - 1, w1 - 1]), int(m[units - 1, w1 - 1])
+
+    best, t = None, int(big) - 1
+    while t >= 0:
+        f, mx = least_sum(t)
+        if f >= big:
+            break
+        obj = f + (micro - 1) * mx
+        if best is None or obj <= best[0]:
+            best = (obj, f, mx)
+        t = min(mx - 1, (best[0] - f) // (micro - 1))   # a lower threshold has a sum >= f
+    return best
+
+
+@pytest.mark.parametrize("layers,pp", [(100, 16), (33, 8)])
+def test_no_windows_against_dense_sweep(torch, layers, pp):
+    """No pruning-1 windows, so that every (level, half-groups) row has the widest band:
+    at 100 layers and 16 stages the state lists and intervals exceed a workgroup's LDS
+    and lie in the workspace (the second work list is not empty), at 33 and 8 they do
+    not.  Whole numbers: every value equal."""
+    p = widths(workloads.random_tiny(61, n_layers=layers, n_types=2, max_pp=pp, micro=[2 * pp]), prune_window=0)
+    p["cluster"]["count"] = np.array([2 * pp, 2 * pp], dtype=np.int32)
+    p["cluster"]["mem_bytes"] = np.array([60, 90], dtype=np.int64) * 10**9
+    p["space"].update(pp_max=pp, tp_mask=1, cp_mask=1, tpe_mask=1, ep_max=1)
+    print(f"widths: {layers} layers, {pp} stages, no windows", flush=True)
+    pl, _ = _run(p)
+    o, res = orc.Oracle(p), pl.results()
+    idx = [int(i) for i in np.nonzero((pl.cand_host["pp"] == pp) & (res["status"] == 0))[0]][:1]
+    assert idx
+    in_ws = int(pl.d_dp_ws[4:8].cpu().numpy().view(np.uint32)[0])
+    assert (in_ws > 0) == (layers == 100)
+    for i in idx:
+        got = tuple(int(res[i][f]) for f in ("objective", "stage_sum", "t_max"))
+        cost, _ = o.width_costs(i)
+        ref = _numpy_sweep(cost, int(pl.cand_host["n_micro"][i]))
+        const = got[0] - got[1] - (int(pl.cand_host["n_micro"][i]) - 1) * got[2]
+        assert got == (ref[0] + const, ref[1], ref[2])
+        cfg, order = i // (o.n_orders() * 1), i % o.n_orders()
+        assert const == o.dp_const(o.configs()[cfg], order)
