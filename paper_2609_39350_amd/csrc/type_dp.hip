@@ -16,9 +16,12 @@
 // b_1, h_1, h_0) among the sum-optimal paths.
 //
 // Thresholds: a pass at t yields the canonical path, whose largest stage m
-// gives the same path for every threshold in [m, t]; so the sweep goes down
-// from t = inf to m - 1 each time, skipping thresholds that can no longer beat
-// any incumbent (F_t >= F_inf).  An incumbent per B is replaced by a lower
+// gives the same path for every threshold in [m, t].  The sweep passes at the
+// least possible largest stage first (one min-max pass finds it), then at
+// infinity, and from there goes down to m - 1 each time, skipping thresholds
+// that can no longer beat any incumbent (the sum only grows); with the
+// incumbent of the first pass, 61 layers, 16 stages and B = 16 to 64 take 9
+// passes a feasible key instead of 48.  An incumbent per B is replaced by a lower
 // objective or an equal one with a lower largest stage: the result is the
 // least sum + (B-1) max, the smallest threshold reaching it, and the
 // back-trace there.  B enters through min(B, PP) (memory) and the objective
@@ -33,16 +36,31 @@
 // levels follow one another with a barrier.  Only end layers b inside the
 // band the pruning-1 windows leave for u are visited (the rest cannot lie on
 // a feasible path).  F and the back-trace pointers live in the workgroup's
-// slice of the workspace; the layer prefix sums, the level lists and the
-// incumbents in LDS.  Plain int64 min-plus work: no MFMA.
+// slice of the workspace, end layers contiguous; the layer prefix sums, the
+// level lists and the incumbents in LDS.  Plain int64 min-plus work: no MFMA.
+// Bound by VALU issue inside the level rounds of the deepest keys (one
+// workgroup a CU, a 16-stage pass of 61 layers: 141 us before, 92 us now): so
+// split points run from the highest, where each next type allows a prefix of
+// them, and a sum carries its split point and type in its low bits.  804 keys,
+// PP <= 16: 12.0 -> 1.95 ms.
+#include <type_traits>
+
 #include "internal.h"
 
 namespace hapmoe {
 namespace {
 
 constexpr int kThreads = 1024;
-constexpr int64_t kNone = INT64_MAX;   // no path
-constexpr int kTypeWin = 4;            // split points a predecessor type loads at once
+constexpr int64_t kNone = INT64_MAX;            // no path in results
+// F, the stage times in LDS and the thresholds are scaled by 2^kKeyBits: a relaxed sum
+// carries its split point and type (a * 4 + h) below, so that one 64-bit minimum also
+// takes the smallest split point, then the smallest type, on equal sums.  A layer's
+// time is below 2^44, 127 layers' below 2^51, so that a path's sum stays below 2^53.
+constexpr int kKeyBits = 9;
+constexpr int64_t kKeyMask = (1 << kKeyBits) - 1;
+constexpr int64_t kFar = int64_t(1) << 62;   // no path in F: above every scaled sum
+static_assert(kMaxLayers * 4 + kMaxTypes <= 1 << kKeyBits, "split point and type");
+constexpr int kTypeWin = 4;                  // split points a predecessor type loads at once
 
 struct TypePath {   // result of one pass, filled by thread 0
     int64_t F, M;
@@ -50,7 +68,7 @@ struct TypePath {   // result of one pass, filled by thread 0
     int32_t s1;         // that stage, 1-based
     uint32_t rmask;
     uint8_t layers[kMaxStages];
-    uint8_t types[kMaxStages];
+    uint8_t types[kMaxStages];   // right after the layers: copied with them
 };
 
 struct TypeInc {   // incumbent of one microbatch count
@@ -61,10 +79,12 @@ struct TypeInc {   // incumbent of one microbatch count
     uint8_t types[kMaxStages];
 };
 
+static_assert(offsetof(TypePath, layers) % 8 == 0 && offsetof(TypeInc, layers) % 8 == 0, "copied in words");
+
 struct TypeCtl {   // workgroup-uniform scalars set by thread 0
     uint32_t qi;
     int32_t go;
-    int64_t t, finf, lastF;
+    int64_t t, tbot, finf;
     int32_t cnt[kMaxStages + 2];   // states per level
     int32_t start[kMaxStages + 2];
     int32_t wmax[kMaxStages + 2];  // widest end-layer band of a level
@@ -115,11 +135,11 @@ __device__ inline int64_t stage_cost(const StageData &D, int h, int a, int b, in
     const int64_t ex = (D.MOE[b] - D.MOE[a]) > 0 ? X : 0;
     if (dw + ms * (D.MA0[b] - D.MA0[a]) + ex <= cap) {
         *r = 0;
-        return D.T0[h * D.W + b] - D.T0[h * D.W + a] + pc;
+        return ((D.T0[h * D.W + b] - D.T0[h * D.W + a]) >> kKeyBits) + pc;
     }
     if (recomp && dw + ms * (D.MA1[b] - D.MA1[a]) + ex <= cap) {
         *r = 1;
-        return D.T1[h * D.W + b] - D.T1[h * D.W + a] + pc;
+        return ((D.T1[h * D.W + b] - D.T1[h * D.W + a]) >> kKeyBits) + pc;
     }
     return kNone;
 }
@@ -245,27 +265,31 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
             sMOE[b] = (int32_t)mem[3 * np + b];
             for (int h = 0; h < T; ++h) {
                 const bool on = k[h] > 0;   // only the sets some stage uses are written
-                sT0[h * W + b] = on ? time[((int64_t)((1 << h) - 1) * 3) * np + b] : 0;
-                sT1[h * W + b] = on ? time[((int64_t)((1 << h) - 1) * 3 + 1) * np + b] : 0;
+                sT0[h * W + b] = on ? time[((int64_t)((1 << h) - 1) * 3) * np + b] << kKeyBits : 0;
+                sT1[h * W + b] = on ? time[((int64_t)((1 << h) - 1) * 3 + 1) * np + b] << kKeyBits : 0;
             }
         }
         __syncthreads();
 
         const int64_t X = pi->x_bytes, eta_tbar = (int64_t)H.eta_prune * pi->tbar;
         const bool recomp = H.allow_recompute != 0, prune_het = H.prune_hetero != 0;
-        // ---- one pass at threshold t, groups of equal min(B, PP) = v ----
-        auto pass = [&](int64_t t, int v) {
+        // ---- one pass at threshold t, groups of equal min(B, PP) = v; MINMAX: the least
+        // possible largest stage instead (no threshold, no back-trace) ----
+        auto pass = [&](auto minmax, int64_t t, int v) {
+            constexpr bool MINMAX = decltype(minmax)::value;
+            const int64_t ts = t >= kFar >> kKeyBits ? kFar : (t << kKeyBits) | kKeyMask;
             uint32_t relax = 0;
             for (int i = tid; i < W * T1; i += kThreads) {   // u = 0: only b = 0
-                const int b = i / T1, hn = i % T1;
-                F[i] = (b == 0 && hn < T && k[hn] > 0) ? 0 : kNone;
+                const int hn = i / W, b = i - hn * W;
+                F[i] = (b == 0 && hn < T && k[hn] > 0) ? 0 : kFar;
             }
             __syncthreads();
             for (int l = 1; l <= PP; ++l) {
                 const int s = l - 1;   // the stage that ends at b
+                const bool last = l == PP;
                 // one (u, b) state vector a thread: its predecessors are loaded once and
-                // relaxed into every valid next type h' (the transfer and pruning 3
-                // depend on h', the rest does not)
+                // relaxed into every next type e (the transfer and pruning 3 depend on e,
+                // the rest does not); the last stage has no successor: slot 0, no transfer
                 const int wm = C.wmax[l];
                 const int n_items = (C.start[l + 1] - C.start[l]) * wm;
                 const float inv_wm = wm ? 1.0f / (float)wm : 0.0f;
@@ -276,166 +300,181 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
                     const int wd = (int)(x >> 45) & 0x1ff;
                     if (j >= wd) continue;
                     const int u = (int)(x & 0x1fff), b = ((int)(x >> 37) & 0xff) + j;
-                    int d[kMaxTypes], ulo = 0, uhi = 0, rlo = 0, rhi = 0, hnmask = 0;
+                    int d[kMaxTypes], ulo = 0, uhi = 0;
 #pragma unroll
                     for (int h = 0; h < kMaxTypes; ++h) {
                         d[h] = (int)(x >> (13 + 6 * h)) & 63;
                         ulo += d[h] * lo[h];
                         uhi += d[h] * hi[h];
-                        rlo += (k[h] - d[h]) * lo[h];
-                        rhi += (k[h] - d[h]) * hi[h];
-                        if (h < T && d[h] < k[h]) hnmask |= 1 << h;   // a stage of type h can follow
                     }
-                    if (l == PP) hnmask = 1 << T;   // the last stage: no successor
-                    int64_t best[kMaxTypes + 1];
-                    int bk[kMaxTypes + 1];
+                    int64_t best[kMaxTypes];
 #pragma unroll
-                    for (int e = 0; e <= kMaxTypes; ++e) {
-                        best[e] = kNone;
-                        bk[e] = 0x7fff;
-                    }
-                    // the first kTypeWin split points of every predecessor type are
-                    // loaded together (up to 16 loads in flight), then relaxed; longer
-                    // windows (no pruning-1 windows) finish in a second loop
-                    int wa0[kMaxTypes], wa1[kMaxTypes];
-                    int64_t pv[kMaxTypes][kTypeWin];
+                    for (int e = 0; e < kMaxTypes; ++e) best[e] = kFar;
 #pragma unroll
                     for (int h = 0; h < kMaxTypes; ++h) {
-                        wa0[h] = 1;
-                        wa1[h] = 0;   // empty
-                        if (h < T && d[h] > 0) {
-                            // the predecessor's band: one stage of type h fewer
-                            const int plo = (ulo - lo[h]) > N - (rhi + hi[h]) ? (ulo - lo[h]) : N - (rhi + hi[h]);
-                            const int phi = (uhi - hi[h]) < N - (rlo + lo[h]) ? (uhi - hi[h]) : N - (rlo + lo[h]);
-                            wa0[h] = (b - hi[h]) > plo ? (b - hi[h]) : plo;
-                            wa1[h] = (b - lo[h]) < phi ? (b - lo[h]) : phi;
-                        }
-                        const int64_t *Fp = F + (int64_t)(u - rad[h]) * W * T1 + h;
-#pragma unroll
-                        for (int jj = 0; jj < kTypeWin; ++jj) {
-                            const int a = wa0[h] + jj;
-                            pv[h][jj] = a <= wa1[h] ? Fp[(int64_t)a * T1] : kNone;
-                        }
-                    }
-#pragma unroll
-                    for (int h = 0; h < kMaxTypes; ++h) {
-                        if (wa0[h] > wa1[h]) continue;
-                        // transfer to each next type, and pruning 3 on it
-                        int64_t pc[kMaxTypes + 1];
-                        int ok = 0;
-#pragma unroll
-                        for (int e = 0; e <= kMaxTypes; ++e) {
-                            pc[e] = e < T ? pi->p2p[h * kMaxTypes + e] : 0;
-                            const bool p3 = prune_het && e < T && e != h && pc[e] > eta_tbar;
-                            if (((hnmask >> e) & 1) && !p3) ok |= 1 << e;
-                        }
-                        if (!ok) continue;
-                        if (STATS) relax += (uint32_t)((wa1[h] - wa0[h] + 1) * __popc(ok));
+                        if (h >= T || d[h] == 0) continue;
+                        // the predecessor's band (one stage of type h fewer) and what fits in memory
                         const int bd = bounds[(s * T + h) * W + b];
-                        const int amin = bd & 0xff, a0 = bd >> 8;
-                        const int64_t tb0 = sT0[h * W + b], tb1 = sT1[h * W + b];
-                        const int64_t *Fp = F + (int64_t)(u - rad[h]) * W * T1 + h;
-                        for (int a = wa0[h]; a <= wa1[h]; ++a) {
-                            const int jj = a - wa0[h];
-                            int64_t prev = kNone;
+                        const int plo = max(ulo - lo[h], N - (sum_hi - uhi + hi[h]));
+                        const int phi = min(uhi - hi[h], N - (sum_lo - ulo + lo[h]));
+                        const int wa0 = max(max(b - hi[h], plo), bd & 0xff), wa1 = min(b - lo[h], phi);
+                        const int fit0 = bd >> 8;
+                        if (wa0 > wa1) continue;
+                        const int64_t *Fp = F + ((int64_t)(u - rad[h]) * T1 + h) * W;
+                        int64_t pv[kTypeWin];   // the last split points, loaded together
 #pragma unroll
-                            for (int q = 0; q < kTypeWin; ++q) prev = jj == q ? pv[h][q] : prev;
-                            if (jj >= kTypeWin) prev = Fp[(int64_t)a * T1];
-                            if (prev == kNone || a < amin) continue;
-                            const int64_t st = a < a0 ? tb1 - sT1[h * W + a] : tb0 - sT0[h * W + a];
-                            const int key2 = a * 8 + h;
+                        for (int q = 0; q < kTypeWin; ++q) pv[q] = wa1 - q >= wa0 ? Fp[wa1 - q] : kFar;
+                        // transfer to each next type, and the stage time that the threshold and
+                        // pruning 3 allow it (negative: none); the same for every lane
+                        int64_t pc[kMaxTypes], lim[kMaxTypes];
 #pragma unroll
-                            for (int e = 0; e <= kMaxTypes; ++e) {
-                                if (!((ok >> e) & 1)) continue;
-                                const int64_t c = st + pc[e];
-                                if (c > t) continue;
-                                const int64_t val = prev + c;
-                                if (val < best[e] || (val == best[e] && key2 < bk[e])) {
-                                    best[e] = val;
-                                    bk[e] = key2;
+                        for (int e = 0; e < kMaxTypes; ++e) {
+                            const int64_t p = last || e >= T ? 0 : pi->p2p[h * kMaxTypes + e];
+                            const bool on = last ? e == 0 : e < T && !(prune_het && e != h && p > eta_tbar);
+                            pc[e] = p << kKeyBits;
+                            lim[e] = on ? ts - pc[e] : -1;
+                        }
+                        const int64_t *t0 = sT0 + h * W, *t1 = sT1 + h * W;
+                        const int64_t tb0 = t0[b], tb1 = t1[b];
+                        // Split points from the highest: the stage time only grows, so each
+                        // next type allows a prefix of them, and its best is the running least
+                        // sum where its prefix ends
+                        int64_t least = kFar, at[kMaxTypes];
+#pragma unroll
+                        for (int e = 0; e < kMaxTypes; ++e) at[e] = kFar;
+                        auto relax_one = [&](int a, int64_t prev) {
+                            const int64_t st = a < fit0 ? tb1 - t1[a] : tb0 - t0[a];
+                            if (MINMAX) {
+#pragma unroll
+                                for (int e = 0; e < kMaxTypes; ++e) {
+                                    if (lim[e] < 0) continue;
+                                    const int64_t c = st + pc[e], m = prev > c ? prev : c;
+                                    best[e] = m < best[e] ? m : best[e];
                                 }
+                                return;
                             }
+                            const int64_t x2 = prev + st + (a * 4 + h);
+                            least = x2 < least ? x2 : least;
+#pragma unroll
+                            for (int e = 0; e < kMaxTypes; ++e) {
+                                const bool on = st <= lim[e];
+                                if (STATS && on) ++relax;
+                                at[e] = on ? least : at[e];
+                            }
+                        };
+#pragma unroll
+                        for (int q = 0; q < kTypeWin; ++q)
+                            if (wa1 - q >= wa0) relax_one(wa1 - q, pv[q]);
+                        for (int a = wa1 - kTypeWin; a >= wa0; --a) relax_one(a, Fp[a]);   // long windows
+                        if (MINMAX) continue;
+#pragma unroll
+                        for (int e = 0; e < kMaxTypes; ++e) {
+                            const int64_t val = at[e] + pc[e];
+                            best[e] = val < best[e] ? val : best[e];
                         }
                     }
-                    const int64_t at = ((int64_t)u * W + b) * T1;
+                    // a stage of type e can follow where one is left; the last level's state is slot T
+                    const int64_t at0 = ((int64_t)u * T1 + (last ? T : 0)) * W + b;
 #pragma unroll
-                    for (int e = 0; e <= kMaxTypes; ++e) {
-                        if (!((hnmask >> e) & 1)) continue;
-                        F[at + e] = best[e];
-                        ARG[at + e] = (int16_t)(best[e] == kNone ? -1 : bk[e]);
+                    for (int e = 0; e < kMaxTypes; ++e) {
+                        if (last ? e > 0 : e >= T || d[e] >= k[e]) continue;
+                        F[at0 + e * W] = MINMAX ? best[e] : best[e] & ~kKeyMask;
+                        if (!MINMAX) ARG[at0 + e * W] = (int16_t)(best[e] & kKeyMask);
                     }
                 }
                 __syncthreads();
             }
+            if (MINMAX) {
+                if (tid == 0) {
+                    const int64_t m = F[((int64_t)(U - 1) * T1 + T) * W + N];
+                    C.tbot = m >= kFar ? kFar : m >> kKeyBits;
+                }
+                __syncthreads();
+                return;
+            }
             if (STATS && relax) atomicAdd(&C.relax, relax);
-            if (tid == 0) {   // back-trace the canonical path
-                const int64_t fe = F[((int64_t)(U - 1) * W + N) * T1 + T];
-                P.F = fe;
-                P.M = 0;
-                P.rmask = 0;
-                P.fwd = 0;
-                P.s1 = 0;
-                if (fe != kNone) {
-                    int u = U - 1, b = N, hn = T;
-                    int64_t fsum = 0, fafter = 0;   // forward times: all stages, those after the first largest
+            // back-trace the canonical path: the lanes of wave 0 follow the one chain of
+            // pointers, lane i keeps stage i, and the stages are evaluated side by side
+            if (tid < 64) {
+                const int64_t fe = F[((int64_t)(U - 1) * T1 + T) * W + N];
+                int64_t c = 0;
+                int r = 0, a = 0, b = 0, h = 0, hn = T;
+                if (fe < kFar) {
+                    int cu = U - 1, cb = N, ch = T;
                     for (int i = PP - 1; i >= 0; --i) {
-                        const int x = ARG[((int64_t)u * W + b) * T1 + hn];
-                        const int a = x >> 3, h = x & 7;
-                        const int64_t msi = (PP - i) < v ? (PP - i) : v;
-                        const int64_t pc = hn < T ? pi->p2p[h * kMaxTypes + hn] : 0;
-                        int r = 0;
-                        const int64_t c = stage_cost(D, h, a, b, msi, H.mem_bytes[h], X, recomp, pc, &r);
-                        if (c >= P.M) {   // ">=": going down, the smaller stage index wins ties
-                            P.M = c;
-                            P.s1 = i + 1;
-                            fafter = fsum;
+                        const int x = ARG[((int64_t)cu * T1 + ch) * W + cb];
+                        if (tid == i) {
+                            a = x >> 2;
+                            b = cb;
+                            h = x & 3;
+                            hn = ch;
                         }
-                        fsum += (c + 2) / 3;
-                        P.layers[i] = (uint8_t)(b - a);
-                        P.types[i] = (uint8_t)h;
-                        P.rmask |= (uint32_t)r << i;
-                        u -= rad[h];
-                        b = a;
-                        hn = h;
+                        cb = x >> 2;
+                        ch = x & 3;
+                        cu -= ch == 0 ? rad[0] : ch == 1 ? rad[1] : ch == 2 ? rad[2] : rad[3];
                     }
-                    P.fwd = fsum - fafter;
+                    if (tid < PP) {
+                        const int64_t msi = (PP - tid) < v ? (PP - tid) : v;
+                        const int64_t pc = hn < T ? pi->p2p[h * kMaxTypes + hn] : 0;
+                        c = stage_cost(D, h, a, b, msi, H.mem_bytes[h], X, recomp, pc, &r);
+                    }
+                }
+                int64_t m = c;
+#pragma unroll
+                for (int dd = 32; dd; dd >>= 1) {
+                    const int64_t y = __shfl_xor(m, dd);
+                    m = y > m ? y : m;
+                }
+                // the first largest stage, and the forward times up to it
+                const int s1 = __ffsll((unsigned long long)__ballot(tid < PP && c == m));
+                int64_t fwd = EXACT && tid < s1 ? (c + 2) / 3 : 0;
+                if (EXACT)
+#pragma unroll
+                    for (int dd = 32; dd; dd >>= 1) fwd += __shfl_xor(fwd, dd);
+                const uint32_t rm = (uint32_t)__ballot(r);
+                if (tid < kMaxStages) {
+                    P.layers[tid] = tid < PP ? (uint8_t)(b - a) : 0;
+                    P.types[tid] = tid < PP ? (uint8_t)h : 0;
+                }
+                if (tid == 0) {
+                    P.F = fe >= kFar ? kNone : fe >> kKeyBits;
+                    P.M = fe >= kFar ? 0 : m;
+                    P.fwd = fwd;
+                    P.s1 = s1;
+                    P.rmask = rm;
                 }
             }
             __syncthreads();
         };
 
+        const int64_t Bj = tid < nB ? H.micro[tid] : 0;   // thread j keeps microbatch count j's incumbent
+        auto copy_path = [&](TypeInc &I, const TypePath &R) {
+            I.M = R.M;
+            I.F = R.F;
+            I.rmask = R.rmask;
+            const auto *src = reinterpret_cast<const uint64_t *>(R.layers);   // layers, then types
+            auto *dst = reinterpret_cast<uint64_t *>(I.layers);
+#pragma unroll
+            for (int i = 0; i < 2 * kMaxStages / 8; ++i) dst[i] = src[i];
+        };
         auto take = [&](int j) {   // thread j: the pass's path for microbatch count j
-            const int64_t B = H.micro[j];
-            const int64_t obj = P.F + (B - 1) * P.M;
+            const int64_t obj = P.F + (Bj - 1) * P.M;
             TypeInc &I = inc[j];
             if (obj < I.obj || (obj == I.obj && P.M < I.M)) {
                 I.obj = obj;
-                I.M = P.M;
-                I.F = P.F;
-                I.rmask = P.rmask;
-                for (int i = 0; i < kMaxStages; ++i) {
-                    I.layers[i] = i < PP ? P.layers[i] : 0;
-                    I.types[i] = i < PP ? P.types[i] : 0;
-                }
+                copy_path(I, P);
             }
         };
 
         // 1F1B: thread j scores a frontier point for microbatch count j (least
         // latency, ties to the lower largest stage)
         auto take_exact = [&](int j, const TypePath &R) {
-            const int64_t B = H.micro[j];
-            const int64_t steady = B - R.s1 - 1 > 0 ? B - R.s1 - 1 : 0;
+            const int64_t steady = Bj - R.s1 - 1 > 0 ? Bj - R.s1 - 1 : 0;
             const int64_t obj = R.F + R.fwd + steady * R.M;
             TypeInc &I = inc[j];
             if (obj < I.obj || (obj == I.obj && R.M < I.M)) {
                 I.obj = obj;
-                I.M = R.M;
-                I.F = R.F;
-                I.rmask = R.rmask;
-                for (int i = 0; i < kMaxStages; ++i) {
-                    I.layers[i] = i < PP ? R.layers[i] : 0;
-                    I.types[i] = i < PP ? R.types[i] : 0;
-                }
+                copy_path(I, R);
             }
         };
 
@@ -523,40 +562,44 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
             __syncthreads();
             int passes = 0;
             if (shape_ok && !EXACT) {
-                pass(kNone, v);
+                // the least possible largest stage, then the path there: its objective bounds
+                // the thresholds that can still win, going down from infinity
+                pass(std::true_type{}, kNone, v);
                 ++passes;
-                if (P.F != kNone) {
+                if (C.tbot < kFar) {
+                    pass(std::false_type{}, C.tbot, v);
+                    ++passes;
                     if (tid < nB && member(tid)) take(tid);
-                    if (tid == 0) {
-                        C.finf = P.F;
-                        C.lastF = P.F;
-                        C.t = P.M - 1;
-                    }
+                    __syncthreads();
+                    pass(std::false_type{}, kNone, v);
+                    ++passes;
+                    if (tid < nB && member(tid)) take(tid);
+                    if (tid == 0) C.finf = P.F;
                     __syncthreads();
                     for (;;) {
-                        if (tid == 0) {
-                            // thresholds above lim_B cannot reach B's incumbent (F_t >= F_inf)
+                        if (tid < 64) {
+                            // a lower threshold has a sum >= the last one: above lim_B it
+                            // cannot reach B's incumbent
                             int64_t lim = -1;
-                            for (int j = 0; j < nB; ++j) {
-                                if (!member(j)) continue;
-                                const int64_t B = H.micro[j];
-                                const int64_t lj = B > 1 ? (inc[j].obj - C.finf) / (B - 1)
-                                                         : (C.lastF == C.finf ? kNone : -1);
-                                lim = lj > lim ? lj : lim;
+                            if (tid < nB && member(tid)) {
+                                const int64_t room = inc[tid].obj - P.F;
+                                lim = room < 0 ? -1 : Bj > 1 ? room / (Bj - 1) : (P.F == C.finf ? kNone : -1);
                             }
-                            C.t = C.t < lim ? C.t : lim;
-                            C.go = C.t >= 0;
+#pragma unroll
+                            for (int dd = 32; dd; dd >>= 1) {
+                                const int64_t y = __shfl_xor(lim, dd);
+                                lim = y > lim ? y : lim;
+                            }
+                            if (tid == 0) {
+                                C.t = P.M - 1 < lim ? P.M - 1 : lim;
+                                C.go = C.t > C.tbot;
+                            }
                         }
                         __syncthreads();
                         if (!C.go) break;
-                        pass(C.t, v);
+                        pass(std::false_type{}, C.t, v);
                         ++passes;
-                        if (P.F == kNone) break;
                         if (tid < nB && member(tid)) take(tid);
-                        if (tid == 0) {
-                            C.lastF = P.F;
-                            C.t = P.M - 1;
-                        }
                         __syncthreads();
                     }
                 }
@@ -565,7 +608,7 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
                 // walk the (max, sum) frontier downwards: the pending point Q is a
                 // frontier point once a pass at its max - 1 has a larger sum, and is
                 // dropped if the sum is the same (a lower max reaches it)
-                pass(kNone, v);
+                pass(std::false_type{}, kNone, v);
                 ++passes;
                 if (P.F != kNone) {
                     if (tid == 0) {
@@ -584,7 +627,7 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
                         }
                         __syncthreads();
                         if (!C.go) break;
-                        pass(C.t, v);
+                        pass(std::false_type{}, C.t, v);
                         ++passes;
                         if (P.F == kNone) break;
                         if (P.F > Q.F && tid < nB && member(tid)) take_exact(tid, Q);
