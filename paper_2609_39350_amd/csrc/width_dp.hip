@@ -35,18 +35,23 @@
 // less); a first pass stores the feasible split points of every (state, width) as
 // an interval, so that later passes read no memory terms; stage times, F of two
 // levels, intervals, lists and back-trace pointers stay in LDS (61 layers, 16 stages:
-// about 60 KB, two workgroups of four waves a CU).  A key that needs more than tier 1
+// about 60 KB, two workgroups of eight waves a CU).  A key that needs more than tier 1
 // is given is left to a last tier of one workgroup a CU, with lists, intervals and
 // pointers in the workgroup's slice of the workspace.  61 layers, 31,296 keys, PP <=
-// 16: 33.0 -> 2.8 ms (one state a lane over the full rectangle, costs from global
-// memory and a one-lane back-trace before).
+// 16: 33.0 -> 2.45 ms (one state a lane over the full rectangle, costs from global
+// memory and a one-lane back-trace before).  Running a window's split points from the
+// highest and leaving at the first above the threshold measured 4 % slower.
 #include "internal.h"
 
 namespace hapmoe {
 namespace {
 
-constexpr int kThreads = 256;
+constexpr int kThreads = 256;     // of a width-table workgroup
+// of a DP workgroup: LDS holds two a CU, and eight waves each hide more of the reads'
+// latency than four (61 layers, PP <= 16: 2.66 against 3.03 ms a call)
+constexpr int kDpThreads = 512;
 constexpr int kLayerSlots = 128;   // >= kMaxLayers + 1
+constexpr int kMemEntries = (3 * kLayerSlots + kDpThreads - 1) / kDpThreads;   // (width, layer) pairs a thread
 
 __device__ inline int lg2i(int v) { return 31 - __clz(v); }
 
@@ -148,32 +153,49 @@ __global__ __launch_bounds__(kThreads) void k_width_tables(const unsigned char *
     }
     __syncthreads();
 
-    // memory prefix sums: one thread a (width, field) row
+    // memory prefix sums, then the stage times of every device-type set at every width:
+    // a wave a row, layers 2 lane and 2 lane + 1 a lane, so that the per-layer terms of a
+    // row are evaluated side by side (one thread a row before: 160 us, now 85, for
+    // 1,304 configurations of 61 layers and 45 rows)
     int64_t *wmem = reinterpret_cast<int64_t *>(tab + L.off_wmem) + cfg * 3 * 4 * np;
-    if (tid < 12) {
-        const int wi = tid / 4, f = tid % 4;
-        int64_t *row = wmem + (wi * 4 + f) * np;
-        int64_t acc = 0;
-        row[0] = 0;
-        for (int l = 0; l < N; ++l) {
-            acc += f < 3 ? s_val[wi][f][l] : (int64_t)(is_moe[l] != 0);
-            row[l + 1] = acc;
+    const int lane = tid & 63, wave = tid >> 6, l0 = 2 * lane;
+    auto put_row = [&](int64_t *row, int64_t v0, int64_t v1) {   // all lanes of the wave
+        int64_t sum = v0 + v1;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int64_t y = __shfl_up(sum, d);
+            if (lane >= d) sum += y;
         }
+        if (lane == 0) row[0] = 0;
+        if (l0 < N) row[l0 + 1] = sum - v1;
+        if (l0 + 1 < N) row[l0 + 2] = sum;
+    };
+    for (int r = wave; r < 12; r += kThreads / 64) {
+        const int wi = r / 4, f = r % 4;
+        int64_t v[2];
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+            v[q] = l0 + q >= N ? 0 : f < 3 ? s_val[wi][f][l0 + q] : (int64_t)(is_moe[l0 + q] != 0);
+        put_row(wmem + (wi * 4 + f) * np, v[0], v[1]);
     }
-    // stage times of every device-type set at every width: one thread a (set, width)
-    // row, the per-layer terms evaluated in order
     int64_t *wtime = reinterpret_cast<int64_t *>(tab + L.off_wtime) + cfg * nm * 3 * 3 * np;
-    for (int i = tid; i < nm * 3; i += kThreads) {
+    // a stage of at most three half-groups holds three types or more only if the
+    // devices of a type fit strictly inside it: no such set is read otherwise
+    int least = H.count[0];
+    for (int h = 1; h < T; ++h) least = H.count[h] < least ? H.count[h] : least;
+    const int most_types = 3 * (H.total_devices / c.pp / 2) >= least + 2 ? T : 2;
+    for (int i = wave; i < nm * 3; i += kThreads / 64) {
         const int m = i / 3 + 1, wi = i % 3;
+        if (__popc(m) > most_types) continue;
         const double r = ratio(wi + 1);
         double alpha, bw;
         set_link(H, m, alpha, bw);
         const double D = ((tok0 * r) * (double)H.hidden) * (double)H.elem_bytes;
-        int64_t *P0 = wtime + ((int64_t)(m - 1) * 3 + wi) * 3 * np;
-        int64_t *P1 = P0 + np, *P2 = P1 + np;
-        int64_t a0 = 0, a1 = 0, a2 = 0;
-        P0[0] = P1[0] = P2[0] = 0;
-        for (int l = 0; l < N; ++l) {
+        int64_t t0[2] = {0, 0}, t1[2] = {0, 0}, cm[2] = {0, 0};
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int l = l0 + q;
+            if (l >= N) continue;
             double a2a, tp;
             if (!is_moe[l]) {
                 a2a = 0.0;
@@ -188,18 +210,17 @@ __global__ __launch_bounds__(kThreads) void k_width_tables(const unsigned char *
             }
             const double cpt =
                 c.cp == 1 ? 0.0 : 3.0 * ((double)(c.cp - 1) * (alpha + ((2.0 * D) / (double)c.tp) / bw));
-            const int64_t comm = qterm(a2a, &s_flag) + qterm(tp, &s_flag) + qterm(cpt, &s_flag);
+            cm[q] = qterm(a2a, &s_flag) + qterm(tp, &s_flag) + qterm(cpt, &s_flag);
             int64_t ce = -1;
             for (int h = 0; h < T; ++h)
                 if ((m >> h) & 1) ce = s_qce[wi][h][l] > ce ? s_qce[wi][h][l] : ce;
-            const int64_t t0 = ce + comm;
-            a0 += t0;
-            a1 += qterm(H.rc_time * (double)t0, &s_flag);
-            a2 += comm;
-            P0[l + 1] = a0;
-            P1[l + 1] = a1;
-            P2[l + 1] = a2;
+            t0[q] = ce + cm[q];
+            t1[q] = qterm(H.rc_time * (double)t0[q], &s_flag);
         }
+        int64_t *P0 = wtime + ((int64_t)(m - 1) * 3 + wi) * 3 * np;
+        put_row(P0, t0[0], t0[1]);
+        put_row(P0 + np, t1[0], t1[1]);
+        put_row(P0 + 2 * np, cm[0], cm[1]);
     }
     if (tid >= 64 && tid < 67) {   // MoE buffers of each width
         const int wi = tid - 64;
@@ -275,7 +296,7 @@ __device__ inline int64_t wave_max(int64_t x)
 // LAST: the tier of the keys whose regions exceed tier 1's LDS; state lists, intervals,
 // back-trace pointers, descriptors and pruning-3 limits in the workgroup's slice
 template <bool STATS, bool LAST>
-__global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__restrict__ img,
+__global__ __launch_bounds__(kDpThreads, 4) void k_width_dp(const unsigned char *__restrict__ img,
                                                        const hapmoe_candidate *__restrict__ cand, TablesLayout L,
                                                        const unsigned char *__restrict__ tab, int64_t first,
                                                        int64_t count, int lds_bytes,
@@ -336,12 +357,12 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
         WLevel *const lev = reinterpret_cast<WLevel *>(smem + o_lev);
         uint8_t *const blo = smem + o_blo, *const bwd = smem + o_bwd, *const lm = smem + o_lm;   // [level][units]
 
-        // memory terms: two (width, layer) entries a thread, in registers
-        int64_t mw[2] = {0, 0}, ma0[2] = {0, 0}, ma1[2] = {0, 0};
+        // memory terms of kMemEntries (width, layer) pairs a thread, in registers
+        int64_t mw[kMemEntries] = {}, ma0[kMemEntries] = {}, ma1[kMemEntries] = {};
         if (status_ok) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int e = tid + q * kThreads, wi = e / W, b = e - wi * W;
+            for (int q = 0; q < kMemEntries; ++q) {
+                const int e = tid + q * kDpThreads, wi = e / W, b = e - wi * W;
                 if (e < 3 * W) {
                     mw[q] = wmem[(wi * 4 + 0) * np + b];
                     ma0[q] = wmem[(wi * 4 + 1) * np + b];
@@ -368,7 +389,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                     if (d < pos_end[j]) t = pos_type[j];
                 return t;
             };
-            for (int i = tid; i < UP * 3; i += kThreads) {
+            for (int i = tid; i < UP * 3; i += kDpThreads) {
                 const int u = i / 3, w = i % 3 + 1;
                 WStage x = {0, 0, 0, 0, 0, 0, 0, 0};
                 if (u + w <= U) {
@@ -425,7 +446,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                 st[i] = x;
             }
         }
-        for (int b = tid; b < W; b += kThreads) {   // [a, b) holds an MoE layer iff a < lm[b]
+        for (int b = tid; b < W; b += kDpThreads) {   // [a, b) holds an MoE layer iff a < lm[b]
             int l = b;
             while (l > 0 && !is_moe[l - 1]) --l;
             lm[b] = (uint8_t)l;
@@ -450,7 +471,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
             const int plane = (PP + 1) * UP;
             const bool ok = status_ok;
             for (int i = 0; ok && i <= PP; ++i) {
-                const int side = tid >> 7, u = tid & 127;   // side 1 walks backwards from the end
+                const int side = (tid >> 7) & 1, u = tid >= 256 ? 127 : tid & 127;   // side 1 walks backwards from the end
                 const int lev = side ? PP - i : i;
                 if (u < UP) {
                     int lo = 255, hi = 0;
@@ -475,7 +496,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                 }
                 __syncthreads();
             }
-            for (int x = tid; ok && x < plane; x += kThreads) {
+            for (int x = tid; ok && x < plane; x += kDpThreads) {
                 int lo = 0, wd = 0;
                 if (reach[x] != 255 && reach[2 * plane + x] != 255) {
                     lo = max((int)reach[x], N - (int)reach[3 * plane + x]);
@@ -489,7 +510,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
         }
         // the states of a level, row after row: one wave a level
         if (status_ok)
-            for (int i = wave; i <= PP; i += kThreads / 64) {
+            for (int i = wave; i <= PP; i += kDpThreads / 64) {
                 const int ul = units_lo(i, PP), nu = level_rows(i, PP);   // at most 33 rows
                 const int wd = lane < nu ? bwd[i * UP + ul + lane] : 0;
                 int sum = wd;
@@ -566,7 +587,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
         if (shape_ok) {
             // stage times: a wave a row
 #pragma unroll 2
-            for (int r = wave; r < n_rows; r += kThreads / 64) {
+            for (int r = wave; r < n_rows; r += kDpThreads / 64) {
                 const int64_t *P = wtime + (int64_t)s_src[r] * 3 * np;
                 const int b0 = lane < W ? lane : 0, b1 = lane + 64 < W ? lane + 64 : 0;
                 const longlong2 x = make_longlong2(P[b0], P[np + b0]), y = make_longlong2(P[b1], P[np + b1]);
@@ -574,7 +595,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                 if (lane + 64 < W) tim[r * W + lane + 64] = y;
             }
             // communication only grows with the layers, so pruning 3 is a least split point
-            for (int m = wave; m < n_mixed; m += kThreads / 64) {
+            for (int m = wave; m < n_mixed; m += kDpThreads / 64) {
                 const WStage &x = st[s_mix[m]];
                 const int64_t *P2 = wtime + ((int64_t)(x.mask - 1) * 9 + (s_mix[m] % 3) * 3 + 2) * np;
                 const int64_t room = eta_tbar - ((x.flags & 2) ? x.p2p : 0);
@@ -585,12 +606,12 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                     am[m * W + b] = (uint8_t)a;
                 }
             }
-            for (int i = tid; i < UP * 3; i += kThreads) {
+            for (int i = tid; i < UP * 3; i += kDpThreads) {
                 const int m = st[i].mask;
                 if (m) st[i].row = (uint16_t)(s_id[(m - 1) * 3 + i % 3] * W);
             }
             // state lists
-            for (int x = tid; x < PP * UP; x += kThreads) {
+            for (int x = tid; x < PP * UP; x += kDpThreads) {
                 const int i = x / UP + 1, u = x - (i - 1) * UP, r = u - units_lo(i, PP);
                 const int wd = bwd[i * UP + u];
                 if (!wd) continue;
@@ -601,7 +622,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
         }
         __syncthreads();
         if (shape_ok)
-            for (int x = tid; x < PP * UP * 3; x += kThreads) {
+            for (int x = tid; x < PP * UP * 3; x += kDpThreads) {
                 const int i = x / (UP * 3) + 1, y = x - (i - 1) * UP * 3, u = y / 3, wi = y - u * 3;
                 const int ul = units_lo(i, PP), u0 = u - wi - 1;
                 if (u < ul || u > units_hi(i, PP)) continue;
@@ -626,8 +647,8 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
         auto put_val = [&](int i) {
             const int64_t ms = (int64_t)(PP - i + 1) < B ? (int64_t)(PP - i + 1) : B;
 #pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                const int e = tid + q * kThreads;
+            for (int q = 0; q < kMemEntries; ++q) {
+                const int e = tid + q * kDpThreads;
                 if (e < 3 * W)
                     val[(i & 1) * 3 * W + e] = make_longlong2(mw[q] + ms * ma0[q], mw[q] + ms * ma1[q]);
             }
@@ -650,7 +671,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                 const int ofs = __builtin_amdgcn_readfirstlane(lv.first), items = __builtin_amdgcn_readfirstlane(lv.n) * 4;
                 const int dofs = __builtin_amdgcn_readfirstlane(lv.rows), ul = __builtin_amdgcn_readfirstlane(lv.ul);
                 if (i < PP) put_val(i + 1);
-                for (int e = tid; e < items; e += kThreads) {
+                for (int e = tid; e < items; e += kDpThreads) {
                     const int q = e & 3, s = e >> 2, wi = q == 3 ? 2 : q;
                     const int x = list[ofs + s], b = x & 127, r = x >> 7;
                     const WDesc d = desc[(dofs + r) * 3 + wi];
@@ -717,7 +738,7 @@ __global__ __launch_bounds__(kThreads) void k_width_dp(const unsigned char *__re
                 const WLevel lv = lev[i];
                 const int ofs = __builtin_amdgcn_readfirstlane(lv.first), items = __builtin_amdgcn_readfirstlane(lv.n) * 4;
                 const int dofs = __builtin_amdgcn_readfirstlane(lv.rows);
-                for (int e = tid; e < items; e += kThreads) {
+                for (int e = tid; e < items; e += kDpThreads) {
                     const int q = e & 3, s = e >> 2, wi = q == 3 ? 2 : q;
                     const int x = list[ofs + s], f = iv[(ofs + s) * 3 + wi];
                     const int b = x & 127, r = x >> 7;
@@ -1017,13 +1038,13 @@ hipError_t launch_width_dp(const hapmoe_problem &p, const void *d_image, const h
                                                      hipFuncAttributeMaxDynamicSharedMemorySize, lds);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kThreads), lds, s, img, d_cand, L, tab, first, count,
+        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(kDpThreads), lds, s, img, d_cand, L, tab, first, count,
                            lds, slots, slot, d_res, d_types, d_widths, d_stats, queue, spill);
         return hipGetLastError();
     };
     const int lds = width_dp_lds_bytes(p, ppmax);
-    int per_cu = 160 * 1024 / (lds + 1024);   // 8 workgroups of 4 waves fill a CU
-    per_cu = per_cu < 1 ? 1 : per_cu > 8 ? 8 : per_cu;
+    int per_cu = 160 * 1024 / (lds + 1024);   // 4 workgroups of 8 waves fill a CU
+    per_cu = per_cu < 1 ? 1 : per_cu > 4 ? 4 : per_cu;
     const int64_t g1 = n_keys < 256 * per_cu ? n_keys : 256 * per_cu;
     const int64_t g2 = n_keys < kWidthDpMaxSlots ? n_keys : kWidthDpMaxSlots;
     if (const hipError_t e = d_stats ? go(k_width_dp<true, false>, lds, g1) : go(k_width_dp<false, false>, lds, g1))
