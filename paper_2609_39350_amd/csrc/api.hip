@@ -456,8 +456,8 @@ int32_t hapmoe_eval_cost_tables(const hapmoe_problem *p, const void *d_image, co
     if (count == 0) return HAPMOE_OK;
     // the configurations holding candidates [first, first + count)
     const int64_t cfg_lo = first / per, cfg_hi = (first + count - 1) / per;
-    if (launch_cost_tables(d_image, d_cand, per, p->model.n_layers, L, cfg_lo, cfg_hi - cfg_lo + 1, d_tables,
-                           d_debug, D, (hipStream_t)stream) != hipSuccess)
+    if (launch_cost_tables(d_image, d_cand, per, p->model.n_layers, p->model.n_experts, L, cfg_lo, cfg_hi - cfg_lo + 1,
+                           d_tables, d_debug, D, (hipStream_t)stream) != hipSuccess)
         return HAPMOE_E_HIP;
     if (p->space.stage_types == 3 &&
         launch_width_tables(d_image, d_cand, per, L, cfg_lo, cfg_hi - cfg_lo + 1, d_tables, (hipStream_t)stream) !=

@@ -2,7 +2,8 @@
 // and the candidate's ordering and B): per configuration pi the best of its
 // candidates, then the global best.  Order: objective, then candidate index.
 // Two kernels: the streaming partial minima over 4,096-candidate chunks, then
-// one workgroup for the per-configuration and global minima and the winner.
+// one workgroup for the per-configuration and global minima and the winner; up to
+// kSmall candidates that workgroup reads the records itself.
 // Reading the 8-byte objective of every 64-byte result record, this is a
 // streaming (HBM-bound) reduction.
 #include <mutex>
@@ -64,8 +65,18 @@ __device__ inline Best block_min(Best v, Best *sh)
     return sh[0];
 }
 
+// a candidate's objective for the arg-min (with a fixed global batch gbs > 0 only the
+// candidates whose B * DP * mbs equals it)
+__device__ inline Best offer(const hapmoe_dp_result *res, const hapmoe_candidate *cand, int64_t i, int64_t gbs,
+                             int64_t mbs)
+{
+    const hapmoe_dp_result &r = res[i];
+    bool take = r.status == HAPMOE_STATUS_OK;
+    if (gbs > 0) take = take && (int64_t)cand[i].n_micro * cand[i].dp * mbs == gbs;
+    return Best{take ? r.objective : kInf, i};
+}
+
 // level 1: chunk ch of configuration cfg -> partial[cfg * chunks + ch]
-// (with a fixed global batch gbs > 0 only the candidates whose B * DP * mbs equals it)
 __global__ __launch_bounds__(kThreads) void k_seg_partial(const hapmoe_dp_result *__restrict__ res,
                                                           const hapmoe_candidate *__restrict__ cand, int64_t n,
                                                           int64_t per, int64_t chunks, int64_t gbs, int64_t mbs,
@@ -78,10 +89,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_partial(const hapmoe_dp_result
     const int64_t hi = lo + kChunk < seg_hi ? lo + kChunk : seg_hi;
     Best v = {kInf, INT64_MAX};
     for (int64_t i = lo + threadIdx.x; i < hi; i += kThreads) {
-        const hapmoe_dp_result &r = res[i];
-        bool take = r.status == HAPMOE_STATUS_OK;
-        if (gbs > 0) take = take && (int64_t)cand[i].n_micro * cand[i].dp * mbs == gbs;
-        const Best o = {take ? r.objective : kInf, i};
+        const Best o = offer(res, cand, i, gbs, mbs);
         if (better(o, v)) v = o;
     }
     v = block_min(v, sh);
@@ -95,22 +103,36 @@ constexpr int kFinishThreads = 1024;
 // levels 2 and 3 in one workgroup: per configuration over its chunks (into
 // config_best), the global best over configurations, then the winner's result,
 // candidate and stage layout copied next to it, so that the host reads
-// everything with one copy.
+// everything with one copy.  Up to kSmall candidates (no partial minima) a thread
+// reads its configuration's records: one launch instead of two, whose gap costs more
+// than the reads (8 layers, 290 candidates).
+constexpr int64_t kSmall = 2048;
+template <bool SMALL>
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const Best *__restrict__ partial, int64_t n_configs,
                                                            int64_t chunks, int64_t *__restrict__ config_best,
                                                            const hapmoe_dp_result *__restrict__ res,
                                                            const hapmoe_candidate *__restrict__ cand,
                                                            const unsigned char *__restrict__ key_info,
                                                            const uint8_t *__restrict__ types, int64_t n_micro,
+                                                           int64_t n, int64_t per, int64_t gbs, int64_t mbs,
                                                            Best *__restrict__ glob, uint32_t *__restrict__ out)
 {
     __shared__ Best sh[kFinishThreads / 64];
     Best v = {kInf, INT64_MAX};
     for (int64_t cfg = threadIdx.x; cfg < n_configs; cfg += kFinishThreads) {
         Best c = {kInf, INT64_MAX};
-        for (int64_t k = 0; k < chunks; ++k) {
-            const Best o = partial[cfg * chunks + k];
-            if (better(o, c)) c = o;
+        if constexpr (SMALL) {
+            const int64_t hi = (cfg + 1) * per < n ? (cfg + 1) * per : n;
+#pragma unroll 4
+            for (int64_t i = cfg * per; i < hi; ++i) {
+                const Best o = offer(res, cand, i, gbs, mbs);
+                if (better(o, c)) c = o;
+            }
+        } else {
+            for (int64_t k = 0; k < chunks; ++k) {
+                const Best o = partial[cfg * chunks + k];
+                if (better(o, c)) c = o;
+            }
         }
         if (config_best) config_best[cfg] = c.obj == kInf ? -1 : c.idx;
         if (better(c, v)) v = c;
@@ -171,10 +193,14 @@ hipError_t launch_best_plan(const hapmoe_dp_result *d_res, const hapmoe_candidat
     Best *glob = static_cast<Best *>(d_ws);
     auto *winner = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(d_ws) + sizeof(Best));
     Best *partial = reinterpret_cast<Best *>(static_cast<unsigned char *>(d_ws) + sizeof(Best) + kWinnerBytes);
-    hipLaunchKernelGGL(k_seg_partial, dim3((unsigned)n_configs, (unsigned)chunks), dim3(kThreads), 0, s, d_res,
-                       d_cand, n, per_config, chunks, global_batch, mbs, partial);
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kFinishThreads), 0, s, partial, n_configs, chunks, d_config_best,
-                       d_res, d_cand, d_key_info, d_types, n_micro, glob, winner);
+    // few records, and few of them a configuration: a thread reads those one after another
+    const bool small = n <= kSmall && per_config <= 16;
+    if (!small)
+        hipLaunchKernelGGL(k_seg_partial, dim3((unsigned)n_configs, (unsigned)chunks), dim3(kThreads), 0, s, d_res,
+                           d_cand, n, per_config, chunks, global_batch, mbs, partial);
+    hipLaunchKernelGGL(small ? k_finish<true> : k_finish<false>, dim3(1), dim3(kFinishThreads), 0, s, partial, n_configs, chunks, d_config_best,
+                       d_res, d_cand, d_key_info, d_types, n_micro, n, per_config, global_batch, mbs, glob,
+                       winner);
     return hipGetLastError();
 }
 

@@ -143,6 +143,8 @@ __global__ __launch_bounds__(kThreads) void k_layer_skew(const unsigned char *__
 // sequence of phases, and 2,510 of them on 256 CUs finish sooner with twice the
 // workgroups resident, even though a few small per-thread arrays then live in
 // scratch (0.105 -> 0.087 ms on the 96-layer MoE workload).
+// OWN_SKEW: the load-imbalance factors here instead of by k_layer_skew
+template <bool OWN_SKEW>
 __global__ __launch_bounds__(kThreads, 8) void k_cost_tables(const unsigned char *__restrict__ img,
                                                           const hapmoe_candidate *__restrict__ cand,
                                                           int64_t per_config, int64_t cfg_lo, TablesLayout L,
@@ -202,7 +204,35 @@ __global__ __launch_bounds__(kThreads, 8) void k_cost_tables(const unsigned char
     }
     // load-imbalance factors (k_layer_skew) and the slowest link of every
     // device-type set
-    for (int l = tid; l < N; l += kThreads) s_skew[l] = reinterpret_cast<const double *>(tab + L.off_layer)[l];
+    if constexpr (OWN_SKEW) {   // eight lanes a layer (launch_cost_tables says when)
+        const int64_t *tokens = reinterpret_cast<const int64_t *>(img + H.off_tokens);
+        const int E = H.n_experts;
+        for (int l = tid >> 3; l < N; l += kThreads / 8) {
+            double sk = 1.0;
+            if (is_moe[l]) {   // the same for the eight
+                int64_t sum = 0, mx = 0;
+                for (int e = tid & 7; e < E; e += 8) {
+                    const int64_t v = tokens[(int64_t)l * E + e];
+                    sum += v;
+                    mx = v > mx ? v : mx;
+                }
+#pragma unroll
+                for (int d = 4; d >= 1; d >>= 1) {
+                    sum += __shfl_xor(sum, d, 64);
+                    const int64_t y = __shfl_xor(mx, d, 64);
+                    mx = y > mx ? y : mx;
+                }
+                const double rho = sum > 0 ? (double)(mx * E) / (double)sum : 1.0;
+                sk = 1.0 + H.gamma * (rho - 1.0);
+            }
+            if ((tid & 7) == 0) {
+                s_skew[l] = sk;
+                if (blockIdx.x == 0) reinterpret_cast<double *>(tab + L.off_layer)[l] = sk;
+            }
+        }
+    } else {
+        for (int l = tid; l < N; l += kThreads) s_skew[l] = reinterpret_cast<const double *>(tab + L.off_layer)[l];
+    }
     if (tid >= 1 && tid < (1 << T)) set_link(H, tid, s_link_a[tid], s_link_b[tid]);
     // the orderings, device counts and speeds, read by the stage layouts below
     if (tid < kMaxOrders * kMaxTypes) s_perm[tid / kMaxTypes][tid % kMaxTypes] = H.perm[tid / kMaxTypes][tid % kMaxTypes];
@@ -551,14 +581,21 @@ __global__ __launch_bounds__(kThreads, 8) void k_cost_tables(const unsigned char
 
 namespace hapmoe {
 
+// Up to kOwnSkew router counts (16 KB) every workgroup of k_cost_tables reduces them
+// itself, eight lanes a layer: that costs less than the launch before it.  With more
+// (61 layers of 256 experts) the layers' factors are worth a kernel of their own.
+constexpr int64_t kOwnSkew = 2048;
+
 hipError_t launch_cost_tables(const void *d_image, const hapmoe_candidate *d_cand, int64_t per_config,
-                              int n_layers, const TablesLayout &L, int64_t cfg_lo, int64_t n_cfg, void *d_tables,
+                              int n_layers, int n_experts, const TablesLayout &L, int64_t cfg_lo, int64_t n_cfg, void *d_tables,
                               double *d_debug, const DebugLayout &D, hipStream_t s)
 {
     if (n_cfg <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_layer_skew, dim3((unsigned)n_layers), dim3(kThreads), 0, s,
-                       static_cast<const unsigned char *>(d_image), L, static_cast<unsigned char *>(d_tables));
-    hipLaunchKernelGGL(k_cost_tables, dim3((unsigned)n_cfg), dim3(kThreads), 0, s,
+    const bool own_skew = (int64_t)n_layers * n_experts <= kOwnSkew;
+    if (!own_skew)
+        hipLaunchKernelGGL(k_layer_skew, dim3((unsigned)n_layers), dim3(kThreads), 0, s,
+                           static_cast<const unsigned char *>(d_image), L, static_cast<unsigned char *>(d_tables));
+    hipLaunchKernelGGL(own_skew ? k_cost_tables<true> : k_cost_tables<false>, dim3((unsigned)n_cfg), dim3(kThreads), 0, s,
                        static_cast<const unsigned char *>(d_image), d_cand, per_config, cfg_lo, L,
                        static_cast<unsigned char *>(d_tables), d_debug, D);
     return hipGetLastError();

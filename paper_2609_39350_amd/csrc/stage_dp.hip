@@ -402,8 +402,13 @@ __device__ inline void write_result(hapmoe_dp_result *out, int status, int64_t o
 
 __global__ void k_reset_queue(uint32_t *q) { q[0] = 0; }
 
-template <bool STATS, bool EXACT>
-__global__ __launch_bounds__(64) void k_stage_dp(const unsigned char *__restrict__ img,
+// The 1F1B walk runs at four waves a SIMD (128 VGPRs, a few registers more than it
+// would take else): 61 layers, B = 16, 32 and 64, 874 -> 820 us a call.  The threshold
+// objective does not (96 layers, B = 1 .. 64: 2.78 ms, and 2.98 at four waves).
+// QUEUE = false: one workgroup a key, which needs no queue and no launch that resets
+// it; a kernel of its own, as the test for it in the other cost 1 % there (96 layers).
+template <bool STATS, bool EXACT, bool QUEUE>
+__global__ __launch_bounds__(64, EXACT ? 4 : 0) void k_stage_dp(const unsigned char *__restrict__ img,
                                                  const hapmoe_candidate *__restrict__ cand, TablesLayout L,
                                                  const unsigned char *__restrict__ tab, int64_t first,
                                                  int64_t count, int64_t key_lo, int64_t n_keys, DpLds S,
@@ -427,11 +432,17 @@ __global__ __launch_bounds__(64) void k_stage_dp(const unsigned char *__restrict
     // Keys come off the queue largest first, one at a time: fetching the next
     // key's index early (to hide the atomic's latency) binds a wave to it too
     // soon and costs more in balance than it saves, at every depth measured.
+    uint32_t own = blockIdx.x;   // QUEUE = false: the key of this workgroup, then past the last
     for (;;) {
         HAPMOE_CLOCK_RESTART();
         HAPMOE_KEY_MARK(lane);
         uint32_t qi = 0;
-        if (lane == 0) qi = atomicAdd(queue, 1u);
+        if constexpr (QUEUE) {
+            if (lane == 0) qi = atomicAdd(queue, 1u);
+        } else {
+            qi = own;
+            own = (uint32_t)n_keys;
+        }
         // wave-uniform from here on: everything indexed by the key stays scalar
         qi = (uint32_t)__builtin_amdgcn_readlane((int)qi, 0);
         if ((int64_t)qi >= n_keys) break;   // every wave exits once the queue is drained
@@ -1580,21 +1591,30 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
     const auto *img = static_cast<const unsigned char *>(d_image);
     const auto *tab = static_cast<const unsigned char *>(d_tables);
     uint32_t *queue = static_cast<uint32_t *>(d_ws);
-    hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, s, queue);
     int dev = 0, ncu = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return hipErrorUnknown;
-    auto go = [&](auto kern) -> hipError_t {
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, S.total);
+    auto go = [&](auto queued, auto direct) -> hipError_t {
+        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, queued, 64, S.total);
         if (e != hipSuccess) return e;
         int64_t grid = (int64_t)ncu * (per_cu > 0 ? per_cu : 1);
-        if (grid > n_keys) grid = n_keys;
-        hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64), S.total, s, img, d_cand, L, tab, first, count,
-                           key_lo, n_keys, S, d_res, d_stats, queue);
+        // every key resident at once: workgroup i takes the i-th largest (8 layers, 290
+        // keys: 79 -> 76 us a call without the queue's reset launch); more keys balance
+        // better off the queue (96 layers, 60,240 keys: 2.45 against 2.55 ms)
+        const bool all = n_keys <= grid;
+        if (all)
+            grid = n_keys;
+        else
+            hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, s, queue);
+        hipLaunchKernelGGL(all ? direct : queued, dim3((unsigned)grid), dim3(64), S.total, s, img, d_cand, L, tab,
+                           first, count, key_lo, n_keys, S, d_res, d_stats, queue);
         return hipGetLastError();
     };
-    if (exact) return d_stats ? go(k_stage_dp<true, true>) : go(k_stage_dp<false, true>);
-    return d_stats ? go(k_stage_dp<true, false>) : go(k_stage_dp<false, false>);
+    if (exact)
+        return d_stats ? go(k_stage_dp<true, true, true>, k_stage_dp<true, true, false>)
+                       : go(k_stage_dp<false, true, true>, k_stage_dp<false, true, false>);
+    return d_stats ? go(k_stage_dp<true, false, true>, k_stage_dp<true, false, false>)
+                   : go(k_stage_dp<false, false, true>, k_stage_dp<false, false, false>);
 }
 
 }  // namespace hapmoe
