@@ -1599,7 +1599,8 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
         if (e != hipSuccess) return e;
         int64_t grid = (int64_t)ncu * (per_cu > 0 ? per_cu : 1);
         // every key resident at once: workgroup i takes the i-th largest (8 layers, 290
-        // keys: 79 -> 76 us a call without the queue's reset launch); more keys balance
+        // keys: without the queue's reset and the two other launches that small calls
+        // save, 79.5 -> 72 us a call); more keys balance
         // better off the queue (96 layers, 60,240 keys: 2.45 against 2.55 ms)
         const bool all = n_keys <= grid;
         if (all)
