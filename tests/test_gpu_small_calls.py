@@ -1,0 +1,65 @@
+"""The launch rules for small calls: the arg-min over few candidates in one
+launch, and the stage DP with one workgroup a key, at and around their limits."""
+import copy
+
+import numpy as np
+import pytest
+
+from paper_2609_39350_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def planner():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    p = copy.deepcopy(workloads.config(2))
+    p["space"]["micro"] = [8]   # six candidates a configuration
+    pl = binding.Planner(p, "cuda:0")
+    pl.run()
+    return pl
+
+
+@pytest.mark.parametrize("n", [1, 5, 6, 7, 2047, 2048, 2049, 5424])
+@pytest.mark.parametrize("batch", [0, 32])
+def test_arg_min_around_the_one_launch_limit(planner, n, batch):
+    """Least (objective, index) of the first n records and of every configuration's,
+    against numpy on the same records; with a fixed global batch only some count."""
+    pl, per = planner, 6
+    print(f"arg-min of {n} records, batch {batch}", flush=True)
+    problem = copy.deepcopy(pl.problem)
+    problem["space"]["global_batch"] = batch
+    res, cand = pl.results()[:n], pl.cand_host[:n]
+    take = res["status"] == 0
+    if batch:
+        take &= cand["n_micro"].astype(np.int64) * cand["dp"] * problem["model"]["micro_batch_size"] == batch
+    obj = np.where(take, res["objective"], np.iinfo(np.int64).max)
+    pl.d_config_best.fill_(-7)
+    try:
+        plan = binding.best_plan(problem, pl.d_cand, pl.d_tables, pl.d_res, n, pl.d_ws, pl.d_config_best)
+        assert take.any() and plan["instance"] == int(np.argmin(obj)) and plan["objective"] == int(obj.min())
+    except binding.HapmoeError as e:
+        assert e.code == -6 and not take.any()
+    got = pl.config_best()
+    for c in range(pl.n_configs):
+        seg = obj[c * per:(c + 1) * per]
+        want = -1 if len(seg) == 0 or seg.min() == np.iinfo(np.int64).max else c * per + int(np.argmin(seg))
+        assert got[c] == want, (c, int(got[c]), want)
+
+
+@pytest.mark.parametrize("objective", ["threshold", "1f1b"])
+def test_stage_dp_one_workgroup_a_key(planner, objective):
+    """Sub-ranges with fewer keys than resident workgroups (no work queue) give the
+    records of the whole launch, which has more."""
+    pl = planner
+    pl.stage_dp(objective=objective)
+    whole = pl.results().copy()
+    pl.d_res.zero_()
+    print(f"stage DP in sub-ranges, {objective}", flush=True)
+    cuts = [0, 1, 64, 65, 1000, 2500, 3999, pl.n]
+    for a, b in zip(cuts[:-1], cuts[1:]):
+        pl.stage_dp(first=a, count=b - a, objective=objective)
+    assert (pl.results() == whole).all()
+    pl.stage_dp()
