@@ -495,8 +495,8 @@ int32_t stage_dp_any(const hapmoe_problem *p, const void *d_image, const hapmoe_
     std::vector<int32_t> cfg_pp(S.cfg.size());
     for (size_t i = 0; i < S.cfg.size(); ++i) cfg_pp[i] = S.cfg[i][0];
     if (launch_stage_dp(d_image, d_cand, p->model.n_layers, p->space.n_micro, cfg_pp, (int)S.n_orders, L,
-                        d_tables, first, count, S.kmax, S.ppmax, d_res, d_stats, d_ws, p->space.micro, exact,
-                        (hipStream_t)stream) != hipSuccess)
+                        d_tables, first, count, S.kmax, S.ppmax, d_res, d_stats, d_ws, p->space.micro,
+                        p->params.prune_window, exact, (hipStream_t)stream) != hipSuccess)
         return HAPMOE_E_HIP;
     return HAPMOE_OK;
 }

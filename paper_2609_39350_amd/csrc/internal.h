@@ -133,7 +133,7 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
                            const std::vector<int32_t> &config_pp, int n_orders, const TablesLayout &L,
                            const void *d_tables, int64_t first, int64_t count, int kmax, int ppmax,
                            hapmoe_dp_result *d_res, int32_t *d_stats, void *d_ws, const int32_t *micro,
-                           bool exact, hipStream_t s);
+                           int prune_window, bool exact, hipStream_t s);
 int64_t stage_dp_ws_bytes();
 // the least 1F1B latency over every partition: one workgroup per key; lds_hint:
 // what latency_dp_lds expects a workgroup to need for the pipeline depths of the space

@@ -402,13 +402,12 @@ __device__ inline void write_result(hapmoe_dp_result *out, int status, int64_t o
 
 __global__ void k_reset_queue(uint32_t *q) { q[0] = 0; }
 
-// The 1F1B walk runs at four waves a SIMD (128 VGPRs, a few registers more than it
-// would take else): 61 layers, B = 16, 32 and 64, 874 -> 820 us a call.  The threshold
-// objective does not (96 layers, B = 1 .. 64: 2.78 ms, and 2.98 at four waves).
 // QUEUE = false: one workgroup a key, which needs no queue and no launch that resets
 // it; a kernel of its own, as the test for it in the other cost 1 % there (96 layers).
-template <bool STATS, bool EXACT, bool QUEUE>
-__global__ __launch_bounds__(64, EXACT ? 4 : 0) void k_stage_dp(const unsigned char *__restrict__ img,
+// WAVES = 4: at most 128 VGPRs, a few fewer than the kernel would take, so that four
+// waves a SIMD fit (launch_stage_dp says when).
+template <bool STATS, bool EXACT, bool QUEUE, int WAVES = 0>
+__global__ __launch_bounds__(64, WAVES) void k_stage_dp(const unsigned char *__restrict__ img,
                                                  const hapmoe_candidate *__restrict__ cand, TablesLayout L,
                                                  const unsigned char *__restrict__ tab, int64_t first,
                                                  int64_t count, int64_t key_lo, int64_t n_keys, DpLds S,
@@ -1578,7 +1577,7 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
                            const std::vector<int32_t> &config_pp, int n_orders, const TablesLayout &L,
                            const void *d_tables, int64_t first, int64_t count, int kmax, int ppmax,
                            hapmoe_dp_result *d_res, int32_t *d_stats, void *d_ws, const int32_t *micro,
-                           bool exact, hipStream_t s)
+                           int prune_window, bool exact, hipStream_t s)
 {
     (void)config_pp;
     (void)micro;
@@ -1594,9 +1593,8 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
     int dev = 0, ncu = 0, per_cu = 0;
     if (hipGetDevice(&dev) != hipSuccess) return hipErrorInvalidDevice;
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return hipErrorUnknown;
-    auto go = [&](auto queued, auto direct) -> hipError_t {
-        hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, queued, 64, S.total);
-        if (e != hipSuccess) return e;
+    auto fit = [&](auto kern) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, S.total); };
+    auto go = [&](auto queued, auto direct) -> hipError_t {   // per_cu: the queued kernel's
         int64_t grid = (int64_t)ncu * (per_cu > 0 ? per_cu : 1);
         // every key resident at once: workgroup i takes the i-th largest (8 layers, 290
         // keys: without the queue's reset and the two other launches that small calls
@@ -1611,11 +1609,32 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
                            first, count, key_lo, n_keys, S, d_res, d_stats, queue);
         return hipGetLastError();
     };
+    if (exact) {
+        // The 1F1B walk with four waves a SIMD: a single wave is slower, so it pays only where
+        // LDS holds all sixteen a CU and there are keys enough to keep them busy to the end,
+        // more of them the longer a key takes (layers, no windows).  us a call with 3 -> 4 waves,
+        // four device types: 61 layers: 516 -> 582 at 21,576 keys, 661 -> 637 at 27,888, 881 ->
+        // 827 at 39,264 (without windows 4,063 -> 4,190 at 27,888, 5,201 -> 5,005 at 39,264);
+        // 32 layers: 218 -> 238 at 6,048 keys, 318 -> 317 at 12,096, 428 -> 417 at 18,144, 651 ->
+        // 614 at 22,752; LDS holds fewer at 80 and 96 layers: 1,458 -> 1,529 and 3,316 -> 3,521;
+        // uniform windows leave walks too short: 590 -> 597 at 39,264 keys.
+        const int64_t size = n_layers < 40 ? 40 : n_layers > 60 ? 60 : n_layers;
+        const int64_t least = 16 * (int64_t)ncu * size * 2 / (prune_window ? 20 : 15);
+        if (prune_window != 2 && n_keys >= least) {
+            const auto four = d_stats ? k_stage_dp<true, true, true, 4> : k_stage_dp<false, true, true, 4>;
+            if (const hipError_t e = fit(four)) return e;
+            if (per_cu >= 16) return go(four, four);   // never resident at once
+        }
+    }
+    auto pick = [&](auto queued, auto direct) -> hipError_t {
+        if (const hipError_t e = fit(queued)) return e;
+        return go(queued, direct);
+    };
     if (exact)
-        return d_stats ? go(k_stage_dp<true, true, true>, k_stage_dp<true, true, false>)
-                       : go(k_stage_dp<false, true, true>, k_stage_dp<false, true, false>);
-    return d_stats ? go(k_stage_dp<true, false, true>, k_stage_dp<true, false, false>)
-                   : go(k_stage_dp<false, false, true>, k_stage_dp<false, false, false>);
+        return d_stats ? pick(k_stage_dp<true, true, true>, k_stage_dp<true, true, false>)
+                       : pick(k_stage_dp<false, true, true>, k_stage_dp<false, true, false>);
+    return d_stats ? pick(k_stage_dp<true, false, true>, k_stage_dp<true, false, false>)
+                   : pick(k_stage_dp<false, false, true>, k_stage_dp<false, false, false>);
 }
 
 }  // namespace hapmoe

@@ -1,5 +1,6 @@
-"""The launch rules for small calls: the arg-min over few candidates in one
-launch, and the stage DP with one workgroup a key, at and around their limits."""
+"""The launch rules that depend on a call's size: the arg-min over few candidates in
+one launch, the stage DP with one workgroup a key, the 1F1B walk with four waves a
+SIMD, at and around their limits."""
 import copy
 
 import numpy as np
@@ -63,3 +64,25 @@ def test_stage_dp_one_workgroup_a_key(planner, objective):
         pl.stage_dp(first=a, count=b - a, objective=objective)
     assert (pl.results() == whole).all()
     pl.stage_dp()
+
+
+@pytest.mark.parametrize("window,least", [(1, 24576), (0, 32768)])
+def test_1f1b_four_waves_a_simd(planner, window, least):
+    """At least `least` keys run the walk built for four waves a SIMD, fewer the other
+    one: both give the same records and statistics (39,264 keys of three counts)."""
+    p = copy.deepcopy(workloads.config(3))
+    p["params"]["prune_window"] = window
+    pl = binding.Planner(p, "cuda:0")
+    pl.eval_cost_tables()
+    print(f"1F1B walk, 39,264 keys, windows {window}", flush=True)
+    pl.stage_dp(objective="1f1b", stats=True)
+    whole, stats = pl.results().copy(), pl.stats().copy()
+    assert (whole["status"] == 0).sum() > 1000
+    cuts = [0, 3 * (least - 1), pl.n] if window else [0, 3 * 7000, 3 * (least + 6000), pl.n]
+    for with_stats in (False, True):
+        pl.d_res.zero_()
+        for a, b in zip(cuts[:-1], cuts[1:]):
+            pl.stage_dp(first=a, count=b - a, objective="1f1b", stats=with_stats)
+            if with_stats:
+                assert (pl.stats()[a:b] == stats[a:b]).all()
+        assert (pl.results() == whole).all()
