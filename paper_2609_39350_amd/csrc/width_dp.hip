@@ -180,13 +180,15 @@ __global__ __launch_bounds__(kThreads) void k_width_tables(const unsigned char *
     }
     int64_t *wtime = reinterpret_cast<int64_t *>(tab + L.off_wtime) + cfg * nm * 3 * 3 * np;
     // a stage of at most three half-groups holds three types or more only if the
-    // devices of a type fit strictly inside it: no such set is read otherwise
+    // devices of a type fit strictly inside it: no such set is read otherwise.  The set
+    // of all types is evaluated all the same: its latency, bandwidth and compute bound
+    // those of every other set, so it marks an overflow whenever any set would.
     int least = H.count[0];
     for (int h = 1; h < T; ++h) least = H.count[h] < least ? H.count[h] : least;
     const int most_types = 3 * (H.total_devices / c.pp / 2) >= least + 2 ? T : 2;
     for (int i = wave; i < nm * 3; i += kThreads / 64) {
         const int m = i / 3 + 1, wi = i % 3;
-        if (__popc(m) > most_types) continue;
+        if (__popc(m) > most_types && m != nm) continue;
         const double r = ratio(wi + 1);
         double alpha, bw;
         set_link(H, m, alpha, bw);

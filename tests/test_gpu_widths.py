@@ -216,3 +216,53 @@ def test_no_windows_against_dense_sweep(torch, layers, pp):
         assert got == (ref[0] + const, ref[1], ref[2])
         cfg, order = i // (o.n_orders() * 1), i % o.n_orders()
         assert const == o.dp_const(o.configs()[cfg], order)
+
+
+def _overflows(o, n_layers, n_types, cfg, masks):
+    """A term of some width on one of the device-type sets reaches the 2^44 limit."""
+    big = 2.0 ** 44
+    for w in (1, 2, 3):
+        for m in masks:
+            for layer in range(n_layers):
+                t = o.width_terms(cfg, layer, m, w)
+                x = [t["mask"][f] for f in ("a2a", "tp", "cp", "t_r1")] + [t["mem"][f] for f in ("w", "a0")]
+                x += [t["type"][h][f] for h in range(n_types) for f in ("comp", "expert")]
+                if max(x) >= big:
+                    return True
+    return False
+
+
+def test_overflow_of_any_type_set(torch):
+    """A configuration is refused (OVERFLOW) if a term of any device-type set leaves the
+    range, also of a set that no stage can hold: the all-to-all of the three types
+    takes the latency of one link and the bandwidth of another, and only with both does
+    it pass 2^44.  Six stages of four devices hold at most two of the types of eight."""
+    p = widths(workloads.random_tiny(5, n_layers=8, n_types=3, max_pp=6, micro=[4, 9]))
+    m, c = p["model"], p["cluster"]
+    m.update(seq_len=512, hidden=256, n_experts=4, top_k=2, micro_batch_size=1, elem_bytes=2)
+    m["is_moe"][:] = 1
+    m["expert_tokens"] = np.full((8, 4), 256, dtype=np.int64)
+    m["params_expert"] = np.full(8, 10**6, dtype=np.int64)
+    c["count"] = np.array([8, 8, 8], dtype=np.int32)
+    c["mem_bytes"] = np.full(3, 10**14, dtype=np.int64)
+    c["alpha"], c["bw"] = np.full((3, 3), 1000.0), np.full((3, 3), 100.0)
+    part = 0.15 * 2.0 ** 44   # four exchanges of either part alone stay below, of both together do not
+    c["alpha"][0, 1] = c["alpha"][1, 0] = part
+    c["bw"][1, 2] = c["bw"][2, 1] = 512 * 2 * 256 * 2 / part
+    p["params"].update(gamma=0.0, prune_window=0, prune_hetero=0, allow_recompute=1, rc_time=1.33)
+    p["space"].update(pp_max=6, tp_mask=1, cp_mask=1, tpe_mask=1, ep_max=2, mode=0)
+    print("widths: terms at the edge of the range", flush=True)
+    pl = binding.Planner(p, "cuda:0")
+    pl.eval_cost_tables()
+    pl.stage_dp()
+    o, res = orc.Oracle(p), pl.results()
+    per = o.n_orders() * 2
+    seen = set()
+    for k, cfg in enumerate(o.configs()):
+        pairs = _overflows(o, 8, 3, cfg, range(1, 7))
+        every = pairs or _overflows(o, 8, 3, cfg, [7])
+        nominal = any(o.dp_const(cfg, order) >= 2 ** 44 for order in range(o.n_orders()))
+        over = res["status"][k * per:(k + 1) * per] == 2
+        assert over.all() == over.any() == (every or nominal), (cfg, every, nominal)
+        seen.add((every, pairs or nominal))
+    assert {(True, False), (False, False)} <= seen   # only the set of three; none at all
