@@ -256,3 +256,22 @@ def test_count_dp_flag_variants(torch, flags):
     pl.stage_dp()
     idx = sorted(set(list(range(0, pl.n, 13)) + [pl.n - 1]))
     compare_types(p, pl, idx, slow=True)
+
+
+@pytest.mark.parametrize("micro", [[1], [1, 1], [1, 2, 3], [2]])
+def test_count_dp_one_micro_batch(torch, micro):
+    """With B = 1 alone the largest stage only breaks ties, and the sweep starts at
+    infinity: two passes where no lower threshold keeps the sum.  With other counts in
+    the same class the least largest stage comes first (three passes at least)."""
+    least = []
+    for s in range(12):
+        p = count_dp(workloads.random_tiny(1100 + s, n_types=2 + s % 2, micro=micro))
+        if orc.Oracle(p).n_instances() == 0:
+            continue
+        pl = binding.Planner(p, "cuda:0")
+        pl.eval_cost_tables()
+        pl.stage_dp(stats=True)
+        compare_types(p, pl, range(pl.n))
+        ok = (pl.results()["status"] == 0) & (pl.cand_host["pp"] > 1)
+        least += pl.stats()[ok, 0].tolist()
+    assert len(least) > 30 and min(least) == (2 if micro[0] == 1 else 3)
