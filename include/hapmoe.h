@@ -371,8 +371,10 @@ int32_t hapmoe_stage_dp_types_ws_bytes(const hapmoe_problem *p, int64_t *bytes);
  * smallest type.  Writes d_res[0 .. count) like hapmoe_stage_dp and
  * d_types[32 * (0 .. count)], the type mask (1 << h_i) of each stage (0 past
  * PP and for infeasible candidates).  d_stats (may be NULL): passes of the
- * candidate's sweep and the relaxations of the sweep on the first candidate
- * that shares it (columns 2, 3 zero).  d_ws (hapmoe_stage_dp_types_ws_bytes)
+ * candidate's sweep (unless min(B, PP) is 1, the first finds the least possible
+ * largest stage) and, on the first candidate that shares the sweep, their
+ * relaxations: the split points of every state's windows, each into every type
+ * that may follow (columns 2, 3 zero).  d_ws (hapmoe_stage_dp_types_ws_bytes)
  * is the kernel's: calls that may overlap need their own.  Asynchronous. */
 int32_t hapmoe_stage_dp_types(const hapmoe_problem *p, const void *d_image,
                               const hapmoe_candidate *d_cand, int64_t n_cand,

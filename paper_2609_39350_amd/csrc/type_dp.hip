@@ -317,8 +317,16 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
                         const int bd = bounds[(s * T + h) * W + b];
                         const int plo = max(ulo - lo[h], N - (sum_hi - uhi + hi[h]));
                         const int phi = min(uhi - hi[h], N - (sum_lo - ulo + lo[h]));
-                        const int wa0 = max(max(b - hi[h], plo), bd & 0xff), wa1 = min(b - lo[h], phi);
+                        const int win = max(b - hi[h], plo), wa0 = max(win, bd & 0xff), wa1 = min(b - lo[h], phi);
                         const int fit0 = bd >> 8;
+                        if (STATS && win <= wa1) {   // split points of the window, each into every next type
+                            int next = last ? 1 : 0;
+#pragma unroll
+                            for (int e = 0; e < kMaxTypes; ++e)
+                                next += !last && e < T && d[e] < k[e] &&
+                                        !(prune_het && e != h && pi->p2p[h * kMaxTypes + e] > eta_tbar);
+                            relax += (uint32_t)((wa1 - win + 1) * next);
+                        }
                         if (wa0 > wa1) continue;
                         const int64_t *Fp = F + ((int64_t)(u - rad[h]) * T1 + h) * W;
                         int64_t pv[kTypeWin];   // the last split points, loaded together
@@ -358,7 +366,6 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
 #pragma unroll
                             for (int e = 0; e < kMaxTypes; ++e) {
                                 const bool on = st <= lim[e];
-                                if (STATS && on) ++relax;
                                 at[e] = on ? least : at[e];
                             }
                         };
@@ -384,6 +391,7 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
                 }
                 __syncthreads();
             }
+            if (STATS && relax) atomicAdd(&C.relax, relax);
             if (MINMAX) {
                 if (tid == 0) {
                     const int64_t m = F[((int64_t)(U - 1) * T1 + T) * W + N];
@@ -392,7 +400,6 @@ __global__ __launch_bounds__(kThreads) void k_type_dp(const unsigned char *__res
                 __syncthreads();
                 return;
             }
-            if (STATS && relax) atomicAdd(&C.relax, relax);
             // back-trace the canonical path: the lanes of wave 0 follow the one chain of
             // pointers, lane i keeps stage i, and the stages are evaluated side by side
             if (tid < 64) {

@@ -275,3 +275,63 @@ def test_count_dp_one_micro_batch(torch, micro):
         ok = (pl.results()["status"] == 0) & (pl.cand_host["pp"] > 1)
         least += pl.stats()[ok, 0].tolist()
     assert len(least) > 30 and min(least) == (2 if micro[0] == 1 else 3)
+
+
+def _relaxations_a_pass(p, tables, cfg, pp):
+    """Split points of every state's windows, times the types that may follow, of one
+    pass over the device-count DP of a configuration (memory and thresholds aside)."""
+    n, t = int(p["model"]["n_layers"]), p["cluster"]["n_types"]
+    k = [int(c) // (int(sum(p["cluster"]["count"])) // pp) for c in p["cluster"]["count"]]
+    key, pi = tables["key"][cfg, 0], tables["pi"][cfg]
+    lo, hi = [0] * t, [0] * t
+    for s in range(pp):
+        h = int(key["mask"][s]).bit_length() - 1
+        lo[h], hi[h] = int(key["lo"][s]), int(key["hi"][s])
+    span = lambda d, w: sum(x * y for x, y in zip(d, w))
+    if not span(k, lo) <= n <= span(k, hi):
+        return 0
+
+    def band(d):
+        left = [x - y for x, y in zip(k, d)]
+        return max(span(d, lo), n - span(left, hi)), min(span(d, hi), n - span(left, lo))
+
+    limit = int(p["params"]["eta_prune"]) * int(pi["tbar"])
+    total = 0
+    for d in np.ndindex(*[x + 1 for x in k]):
+        if not any(d):
+            continue
+        b0, b1 = band(d)
+        for h in range(t):
+            if d[h] == 0:
+                continue
+            q0, q1 = band([x - (g == h) for g, x in enumerate(d)])
+            follow = 1 if sum(d) == pp else sum(
+                d[e] < k[e] and not (p["params"]["prune_hetero"] and e != h and int(pi["p2p"][4 * h + e]) > limit)
+                for e in range(t))
+            total += follow * sum(max(0, min(b - lo[h], q1) - max(b - hi[h], q0) + 1) for b in range(b0, b1 + 1))
+    return total
+
+
+@pytest.mark.parametrize("objective", ["threshold", "1f1b"])
+def test_count_dp_statistics(torch, objective):
+    """d_stats: every pass counts the split points of all windows into every type that
+    may follow, once for each shared sweep, on its first candidate."""
+    counted = 0
+    problems = [workloads.config(1)] + [workloads.random_tiny(1200 + s, n_types=2 + s % 2, micro=[1, 2, 3, 8])
+                                        for s in range(8)]
+    for p in map(count_dp, problems):
+        if orc.Oracle(p).n_instances() == 0:
+            continue
+        pl = binding.Planner(p, "cuda:0")
+        pl.eval_cost_tables()
+        pl.stage_dp(stats=True, objective=objective)
+        tables, st, nb = binding.decode_tables(p, pl.tables()), pl.stats(), len(p["space"]["micro"])
+        assert not st[:, 2:].any()
+        for cfg in range(pl.n_configs):
+            one = _relaxations_a_pass(p, tables, cfg, int(pl.cand_host["pp"][cfg * nb]))
+            rows = st[cfg * nb:(cfg + 1) * nb]
+            assert (rows[0, 1] > 0) == (one > 0 and rows[0, 0] > 0)
+            for passes, relax in rows[:, :2].tolist():
+                assert relax in (0, passes * one), (p["name"], cfg, passes, relax, one)
+                counted += relax > 0
+    assert counted > 30
