@@ -22,8 +22,8 @@
 // possible largest stage (one min-max pass).  Sweeping every distinct stage
 // cost instead, as the definition does, took 190 passes a feasible 16- or
 // 32-stage candidate of the 96-layer workload; the ranges take 10 to 20, in two
-// to four rounds (96 layers, B = 32 and 64: 63.4 -> 2.9 ms; 61 layers, B = 16,
-// 32 and 64: 4.2 -> 0.73 ms).  The partition itself comes from one exact pass at
+// to four rounds (a call at 96 layers, B = 32 and 64: 64.4 -> 2.8 ms; at 61 layers,
+// B = 16, 32 and 64: 4.24 -> 0.84 ms).  The partition itself comes from one exact pass at
 // the winning t: its back-trace keeps the set of (end layer, z) states on
 // optimal paths and takes, stage by stage from the last, the smallest split
 // point through which one continues optimally.
@@ -520,7 +520,7 @@ __global__ __launch_bounds__(kLatThreads, 4) void k_latency_dp(const unsigned ch
                 int64_t my_lo = 0, my_hi = 0;   // lane i: the i-th slot's range and B
                 int my_B = 1;
                 if (wave == 0) {
-                    // first ranges: [t_bot, t_bot], then up to t_bot (1 + 2^-7), 2^-6, ... 2^-1, and the rest
+                    // first ranges: [t_bot, t_bot], then up to t_bot (1 + 2^-7), 2^-6, ... 2^-2, and the rest
                     if (lane < 8) {
                         const int64_t top = (int64_t)D.cmax;
                         const int64_t a = lane == 0 ? tbot : tbot + (lane == 1 ? 0 : (tbot >> (9 - lane))) + 1;
@@ -539,7 +539,9 @@ __global__ __launch_bounds__(kLatThreads, 4) void k_latency_dp(const unsigned ch
                         bool run = false;
                         while (!run) {
                             if (scan) {
-                                // the next distinct stage costs of range 0, as many as there are slots
+                                // the next distinct stage costs of range 0, as many as there are slots.
+                                // To its end: of 116,000 modelled searches 233 came here, and leaving
+                                // when no member can gain any more would have saved two passes in one
                                 int nt = 0;
                                 const int64_t top = D.nhi[0];
                                 for (; nt < nslot; ++nt) {

@@ -14,6 +14,7 @@ import pytest
 
 from oracle import oracle as orc
 from paper_2609_39350_amd import binding, workloads
+from tests.latency_model import Search, cost
 from tests.problems import variant, worked_problem, worked_problem_w2
 
 pytestmark = pytest.mark.gpu
@@ -249,3 +250,33 @@ def test_latency_ranges(torch, n_layers, max_pp, scale, ties):
     pl, res = run_latency(p)
     idx = np.linspace(0, pl.n - 1, min(pl.n, 1500)).astype(np.int64)
     assert compare(p, res, sorted(set(int(i) for i in idx))) > 0
+
+
+# searches that keep more open ranges than the list allows and sweep one of them
+# threshold by threshold: (configuration, key)
+SWEPT = [(4, 36303), (4, 36903), (4, 38774), (4, 26113), (3, 31617), (3, 38109)]
+
+
+@pytest.mark.parametrize("n,key", SWEPT)
+def test_latency_ranges_swept_by_threshold(torch, n, key):
+    """The search of every B above the depth takes exactly the passes of its model, some
+    of them single thresholds, and finds the model's latencies; the partition is the
+    oracle's for the least, a middle and the largest B."""
+    p = variant(workloads.config(n), **{"space.micro": list(range(1, 65))})
+    o = orc.Oracle(p)
+    cfg, order = o.configs()[key // o.n_orders()], key % o.n_orders()
+    pp, members = cfg[0], list(range(cfg[0] + 1, 65))
+    print(f"least latency: config {n}, key {key}, {pp} stages", flush=True)
+    stages = o.stages(cfg, order, members[0])
+    table, _ = o.segment_costs(key * 64 + pp)
+    best, passes, swept = Search(table, [s["lo"] for s in stages], [s["hi"] for s in stages], members).run()
+    assert swept > 0
+    pl = binding.Planner(p, "cuda:0")
+    pl.eval_cost_tables()
+    pl.stage_dp(first=key * 64, count=64, stats=True, objective="latency")
+    at = slice(key * 64 + pp, key * 64 + 64)
+    res, const = pl.results(), o.dp_const(cfg, order)
+    assert res["objective"][at].tolist() == [t + const for t, _ in best]
+    assert res["t_max"][at].tolist() == [cost(w) for _, w in best]
+    assert set(pl.stats()[at, 0].tolist()) == {passes}
+    assert compare(p, res, [at.start, (at.start + at.stop) // 2, at.stop - 1]) == 3
