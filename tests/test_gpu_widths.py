@@ -187,7 +187,8 @@ def _numpy_sweep(cost, micro):
         obj = f + (micro - 1) * mx
         if best is None or obj <= best[0]:
             best = (obj, f, mx)
-        t = min(mx - 1, (best[0] - f) // (micro - 1))   # a lower threshold has a sum >= f
+        # a lower threshold has a sum >= f
+        t = min(mx - 1, (best[0] - f) // (micro - 1)) if micro > 1 else (mx - 1 if f == best[0] else -1)
     return best
 
 
@@ -266,3 +267,83 @@ def test_overflow_of_any_type_set(torch):
         assert over.all() == over.any() == (every or nominal), (cfg, every, nominal)
         seen.add((every, pairs or nominal))
     assert {(True, False), (False, False)} <= seen   # only the set of three; none at all
+
+
+def _canonical_path(cost, flags, t):
+    """The least-sum path at threshold t: from the last stage the smallest split point,
+    then the smallest width.  (layers, widths, recomputation) of every stage."""
+    big = np.int64(1) << 60
+    pp, units, _, w1, _ = cost.shape
+    f = np.full((pp + 1, units, w1), big)
+    f[0, 0, 0] = 0
+    for s in range(pp):
+        for w in (1, 2, 3):
+            for u in range(units - w):
+                if f[s, u].min() < big:
+                    c = cost[s, u, w - 1]
+                    v = np.where(c <= t, np.minimum(f[s, u][:, None] + np.minimum(c, big), big), big).min(axis=0)
+                    f[s + 1, u + w] = np.minimum(f[s + 1, u + w], v)
+    b, u, path = w1 - 1, units - 1, []
+    for s in range(pp - 1, -1, -1):
+        a, w = next((a, w) for a in range(b) for w in (1, 2, 3)
+                    if u >= w and f[s, u - w, a] < big and cost[s, u - w, w - 1, a, b] <= t
+                    and f[s, u - w, a] + cost[s, u - w, w - 1, a, b] == f[s + 1, u, b])
+        path.append((b - a, w, int(flags[s, u - w, w - 1, a, b]), u - w))
+        b, u = a, u - w
+    return path[::-1]
+
+
+@pytest.mark.parametrize("counts", [[256, 256], [256, 128, 128]])
+def test_partitions_of_the_last_tier(torch, counts):
+    """100 layers, 16 stages, no windows: more keys with their lists in the workspace
+    than it has slices, each with four groups of equal min(B, PP).  Layers, widths,
+    stage types and recomputation against the canonical path on the oracle's costs, and
+    the whole launch against launches of a few keys."""
+    micro = [1, 5, 16, 40, 16]
+    p = widths(workloads.random_tiny(61, n_layers=100, n_types=len(counts), max_pp=16, micro=micro), prune_window=0,
+               allow_recompute=1)
+    m, c = p["model"], p["cluster"]
+    m.update(n_experts=8, top_k=2, hidden=512, seq_len=1024)
+    m["expert_tokens"] = np.full((100, 8), 256, dtype=np.int64)
+    m["is_moe"] = (np.arange(100) % 3 > 0).astype(np.uint8)
+    c["count"] = np.array(counts, dtype=np.int32)
+    c["mem_bytes"] = np.array([60, 90, 75][:len(counts)], dtype=np.int64) * 10**9
+    p["space"].update(pp_max=16, tp_mask=15, cp_mask=15, tpe_mask=15, ep_max=8, mode=0)
+    print(f"widths: last tier, devices {counts}", flush=True)
+    pl = binding.Planner(p, "cuda:0")
+    pl.eval_cost_tables()
+    pl.stage_dp()
+    in_ws = int(pl.d_dp_ws[4:8].cpu().numpy().view(np.uint32)[0])
+    assert in_ws > 256
+    res, types, wd = pl.results().copy(), pl.stage_types().copy(), pl.widths().copy()
+    deep = np.nonzero(pl.cand_host["pp"] == 16)[0]
+    first, n = int(deep[0]), len(deep)
+    for x in (pl.d_res, pl.d_types, pl.d_widths):
+        x[first * x.numel() // pl.n:].zero_()
+    for at in range(first, first + n, 5 * 150):   # whole keys, at most 150 a launch
+        pl.stage_dp(first=at, count=min(5 * 150, first + n - at))
+    assert (pl.results() == res).all()
+    assert (pl.stage_types() == types).all() and (pl.widths() == wd).all()
+
+    o = orc.Oracle(p)
+    per = o.n_orders() * len(micro)
+    key = deep.reshape(-1, 5)
+    ok = (res["status"][key] == 0).all(axis=1)
+    mixed = (res["recompute_mask"][key[:, 2]] > 0) & ok   # recomputes somewhere
+    keys = [key[np.nonzero(mixed)[0][0]], key[np.nonzero(mixed)[0][-1]]]
+    recomputed = 0
+    for i in [int(keys[0][0]), int(keys[0][1]), int(keys[0][2]), int(keys[0][3]), int(keys[1][2])]:
+        cfg, order = o.configs()[i // per], i % per // len(micro)
+        cost, flags = o.width_costs(i)
+        b = int(pl.cand_host["n_micro"][i])
+        obj, total, largest = _numpy_sweep(cost, b)
+        path = _canonical_path(cost, flags, largest)
+        got = res[i]
+        assert (int(got["stage_sum"]), int(got["t_max"])) == (total, largest)
+        assert int(got["objective"]) == obj + o.dp_const(cfg, order)
+        assert got["layers"][:16].tolist() == [x[0] for x in path] and wd[i][:16].tolist() == [x[1] for x in path]
+        assert [(int(got["recompute_mask"]) >> s) & 1 for s in range(16)] == [x[2] for x in path]
+        assert types[i][:16].tolist() == [o.width_stage(cfg, order, s, x[3], x[1], b)["mask"] for s, x in enumerate(path)]
+        recomputed += sum(x[2] for x in path)
+    same = key[ok]   # the two candidates with B = 16
+    assert (res[same[:, 2]] == res[same[:, 4]]).all() and recomputed > 0
