@@ -402,8 +402,9 @@ __device__ inline void write_result(hapmoe_dp_result *out, int status, int64_t o
 
 __global__ void k_reset_queue(uint32_t *q) { q[0] = 0; }
 
-// QUEUE = false: one workgroup a key, which needs no queue and no launch that resets
-// it; a kernel of its own, as the test for it in the other cost 1 % there (96 layers).
+// QUEUE = false: one workgroup a key (launch_stage_dp says when), which needs no queue
+// and no launch that resets it; a kernel of its own, as the test for it in the other
+// cost 1 % there (96 layers).
 // WAVES = 4: at most 128 VGPRs, a few fewer than the kernel would take, so that four
 // waves a SIMD fit (launch_stage_dp says when).
 template <bool STATS, bool EXACT, bool QUEUE, int WAVES = 0>
@@ -1595,17 +1596,24 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
     if (hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) return hipErrorUnknown;
     auto fit = [&](auto kern) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, S.total); };
     auto go = [&](auto queued, auto direct) -> hipError_t {   // per_cu: the queued kernel's
+        // One workgroup a key (the i-th takes the i-th largest) or resident workgroups that
+        // fetch keys off the queue.  The fetches are one chain of atomics, about 5 ns each, that
+        // short keys wait for; the dispatcher deals keys to the XCDs in turn whatever they take,
+        // which costs where keys are long.  us a call, queue -> a workgroup a key: 32 layers,
+        // 5,424 keys: 177 -> 116; 61 layers, 39,264: 634 -> 416; sequences, 118,440: 1,678 -> 789;
+        // 96 layers and 32 stages, 60,240: 1,250 -> 1,111 with two counts B, but 2,644 -> 2,773
+        // with 64 of them (another 56,400 keys: 1,842 -> 1,809 with sixteen).  The 1F1B walk, 32
+        // layers, 5,424 keys: 203 -> 166; 61 layers and 16 stages: 831 -> 726; 72: 1,347 -> 1,309;
+        // 80: 1,457 -> 1,462; 96 layers, 8 stages: 1,063 -> 940, 16: 1,586 -> 1,644, 32: 3,322 ->
+        // 3,643; without windows, 32 layers and 8 stages: 2,027 -> 2,055.  Up to 3.9 keys a resident
+        // workgroup gained in every call measured (8 to 127 layers, both objectives).
         int64_t grid = (int64_t)ncu * (per_cu > 0 ? per_cu : 1);
-        // every key resident at once: workgroup i takes the i-th largest (8 layers, 290
-        // keys: without the queue's reset and the two other launches that small calls
-        // save, 79.5 -> 72 us a call); more keys balance
-        // better off the queue (96 layers, 60,240 keys: 2.45 against 2.55 ms)
-        const bool all = n_keys <= grid;
-        if (all)
-            grid = n_keys;
-        else
-            hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, s, queue);
-        hipLaunchKernelGGL(all ? direct : queued, dim3((unsigned)grid), dim3(64), S.total, s, img, d_cand, L, tab,
+        const bool few = n_keys <= 4 * grid;
+        const bool brief = exact ? prune_window != 0 && n_layers * ppmax <= 1152 : ppmax <= 16 || n_micro <= 8;
+        const bool each = (few || brief) && n_keys < int64_t(1) << 26;   // 2^32 threads are too many to launch
+        if (each || n_keys < grid) grid = n_keys;
+        if (!each) hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, s, queue);
+        hipLaunchKernelGGL(each ? direct : queued, dim3((unsigned)grid), dim3(64), S.total, s, img, d_cand, L, tab,
                            first, count, key_lo, n_keys, S, d_res, d_stats, queue);
         return hipGetLastError();
     };
@@ -1613,17 +1621,17 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
         // The 1F1B walk with four waves a SIMD: a single wave is slower, so it pays only where
         // LDS holds all sixteen a CU and there are keys enough to keep them busy to the end,
         // more of them the longer a key takes (layers, no windows).  us a call with 3 -> 4 waves,
-        // four device types: 61 layers: 516 -> 582 at 21,576 keys, 661 -> 637 at 27,888, 881 ->
-        // 827 at 39,264 (without windows 4,063 -> 4,190 at 27,888, 5,201 -> 5,005 at 39,264);
-        // 32 layers: 218 -> 238 at 6,048 keys, 318 -> 317 at 12,096, 428 -> 417 at 18,144, 651 ->
-        // 614 at 22,752; LDS holds fewer at 80 and 96 layers: 1,458 -> 1,529 and 3,316 -> 3,521;
-        // uniform windows leave walks too short: 590 -> 597 at 39,264 keys.
+        // four device types: 61 layers: 519 -> 540 at 21,576 keys, 645 -> 591 at 27,888, 827 ->
+        // 741 at 39,264 (without windows 4,100 -> 4,195 at 27,888, 5,222 -> 5,007 at 39,264);
+        // 32 layers: 184 -> 193 at 6,048 keys, 340 -> 317 at 18,144, 583 -> 526 at 22,752; LDS
+        // holds fewer at 80 and 96 layers: 1,466 -> 1,574 and 3,655 -> 3,969.
         const int64_t size = n_layers < 40 ? 40 : n_layers > 60 ? 60 : n_layers;
         const int64_t least = 16 * (int64_t)ncu * size * 2 / (prune_window ? 20 : 15);
-        if (prune_window != 2 && n_keys >= least) {
+        if (n_keys >= least) {
             const auto four = d_stats ? k_stage_dp<true, true, true, 4> : k_stage_dp<false, true, true, 4>;
             if (const hipError_t e = fit(four)) return e;
-            if (per_cu >= 16) return go(four, four);   // never resident at once
+            if (per_cu >= 16)
+                return go(four, d_stats ? k_stage_dp<true, true, false, 4> : k_stage_dp<false, true, false, 4>);
         }
     }
     auto pick = [&](auto queued, auto direct) -> hipError_t {

@@ -86,3 +86,22 @@ def test_1f1b_four_waves_a_simd(planner, window, least):
             if with_stats:
                 assert (pl.stats()[a:b] == stats[a:b]).all()
         assert (pl.results() == whole).all()
+
+
+@pytest.mark.parametrize("objective", ["threshold", "1f1b"])
+def test_work_queue_and_a_workgroup_a_key(planner, objective):
+    """60,240 keys of 64 counts, up to 32 stages, go through the work queue; a few
+    thousand of them, the deepest, the shallowest and some between, one workgroup each."""
+    p = copy.deepcopy(workloads.config(4))
+    pl = binding.Planner(p, "cuda:0")
+    pl.eval_cost_tables()
+    print(f"stage DP, 60,240 keys and 2,000, {objective}", flush=True)
+    pl.stage_dp(objective=objective)
+    whole = pl.results().copy()
+    assert (whole["status"] == 0).sum() > 10**6
+    for first, count in ((0, 128000), (1900003, 128001), (pl.n - 128000, 128000)):
+        pl.d_res.zero_()
+        pl.stage_dp(first=first, count=count, objective=objective)
+        part = pl.results()
+        assert (part[first:first + count] == whole[first:first + count]).all()
+        assert not part[:first]["layers"].any() and not part[first + count:]["layers"].any()
