@@ -103,10 +103,13 @@ constexpr int kFinishThreads = 1024;
 // levels 2 and 3 in one workgroup: per configuration over its chunks (into
 // config_best), the global best over configurations, then the winner's result,
 // candidate and stage layout copied next to it, so that the host reads
-// everything with one copy.  Up to kSmall candidates (no partial minima) a thread
-// reads its configuration's records: one launch instead of two, whose gap costs more
-// than the reads (8 layers, 290 candidates).
-constexpr int64_t kSmall = 2048;
+// everything with one copy.  Up to kSmall candidates (no partial minima), at most
+// kSmallSegment a configuration, a thread reads its configuration's records: one launch
+// instead of two, whose gap costs more than the reads.  us of the call, two launches ->
+// one, at 290, 2,048, 4,096 and 8,192 candidates: 6 a configuration 36.3 -> 31.9, 36.2 ->
+// 32.7, 36.1 -> 33.8; 16: 36.0 -> 33.6, 35.9 -> 33.7, 35.9 -> 34.3, 36.0 -> 36.0; 24: 36.1 ->
+// 35.5, 36.3 -> 35.5, 36.3 -> 35.9, 36.2 -> 36.7; 48: 36.1 -> 38.7, 36.2 -> 38.9.
+constexpr int64_t kSmall = 4096, kSmallSegment = 24;
 template <bool SMALL>
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const Best *__restrict__ partial, int64_t n_configs,
                                                            int64_t chunks, int64_t *__restrict__ config_best,
@@ -194,7 +197,7 @@ hipError_t launch_best_plan(const hapmoe_dp_result *d_res, const hapmoe_candidat
     auto *winner = reinterpret_cast<uint32_t *>(static_cast<unsigned char *>(d_ws) + sizeof(Best));
     Best *partial = reinterpret_cast<Best *>(static_cast<unsigned char *>(d_ws) + sizeof(Best) + kWinnerBytes);
     // few records, and few of them a configuration: a thread reads those one after another
-    const bool small = n <= kSmall && per_config <= 16;
+    const bool small = n <= kSmall && per_config <= kSmallSegment;
     if (!small)
         hipLaunchKernelGGL(k_seg_partial, dim3((unsigned)n_configs, (unsigned)chunks), dim3(kThreads), 0, s, d_res,
                            d_cand, n, per_config, chunks, global_batch, mbs, partial);

@@ -23,13 +23,9 @@ def planner():
     return pl
 
 
-@pytest.mark.parametrize("n", [1, 5, 6, 7, 2047, 2048, 2049, 5424])
-@pytest.mark.parametrize("batch", [0, 32])
-def test_arg_min_around_the_one_launch_limit(planner, n, batch):
+def check_arg_min(pl, per, n, batch):
     """Least (objective, index) of the first n records and of every configuration's,
     against numpy on the same records; with a fixed global batch only some count."""
-    pl, per = planner, 6
-    print(f"arg-min of {n} records, batch {batch}", flush=True)
     problem = copy.deepcopy(pl.problem)
     problem["space"]["global_batch"] = batch
     res, cand = pl.results()[:n], pl.cand_host[:n]
@@ -48,6 +44,48 @@ def test_arg_min_around_the_one_launch_limit(planner, n, batch):
         seg = obj[c * per:(c + 1) * per]
         want = -1 if len(seg) == 0 or seg.min() == np.iinfo(np.int64).max else c * per + int(np.argmin(seg))
         assert got[c] == want, (c, int(got[c]), want)
+
+
+@pytest.mark.parametrize("n", [1, 5, 6, 7, 2047, 2048, 2049, 5424])
+@pytest.mark.parametrize("batch", [0, 32])
+def test_arg_min_around_the_one_launch_limit(planner, n, batch):
+    print(f"arg-min of {n} records, batch {batch}", flush=True)
+    check_arg_min(planner, 6, n, batch)
+
+
+@pytest.mark.parametrize("counts", [4, 5])   # 24 candidates a configuration, one launch up to 4,096; 30, two
+@pytest.mark.parametrize("n", [23, 25, 4095, 4096, 4097, 8000])
+def test_arg_min_of_long_segments(planner, counts, n):
+    p = copy.deepcopy(planner.problem)
+    p["space"]["micro"] = [8, 16, 32, 64, 128][:counts]
+    pl = binding.Planner(p, "cuda:0")
+    pl.run()
+    print(f"arg-min of {n} records, {6 * counts} a configuration", flush=True)
+    check_arg_min(pl, 6 * counts, n, 0)
+
+
+@pytest.mark.parametrize("layers,experts", [(32, 64), (33, 64), (33, 32), (32, 72), (8, 256), (127, 16), (9, 0)])
+def test_load_imbalance_factors_of_either_kernel(planner, layers, experts):
+    """1 + gamma (rho - 1) of every layer, reduced by the cost-table workgroups (at most
+    eight counts a lane) or by a kernel before them."""
+    e = max(experts, 1)
+    p = workloads.random_tiny(40 + layers, n_layers=layers, n_types=2)
+    rng = np.random.default_rng(layers * 1000 + experts)
+    p["model"].update(n_experts=experts, top_k=1)
+    p["model"]["is_moe"] = (rng.random(layers) < 0.8).astype(np.uint8) * (experts > 0)
+    p["model"]["params_expert"] = np.where(p["model"]["is_moe"], 10**6, 0).astype(np.int64)
+    tokens = rng.integers(0, 1000, size=(layers, e)).astype(np.int64)
+    p["model"]["expert_tokens"] = tokens if experts else np.zeros((layers, 0), dtype=np.int64)
+    p["params"]["gamma"] = 0.5
+    print(f"load imbalance, {layers} layers x {experts} experts", flush=True)
+    pl = binding.Planner(p, "cuda:0")
+    pl.eval_cost_tables()
+    layout = binding.tables_layout(p)
+    at = -(-(layout["off_time"] + layout["n_configs"] * layout["n_masks"] * 3 * layout["np"] * 8) // 256) * 256
+    got = pl.tables()[at:at + 8 * layers].view(np.float64)
+    rho = (tokens.max(axis=1) * e).astype(np.float64) / tokens.sum(axis=1).astype(np.float64)
+    want = np.where(p["model"]["is_moe"], 1.0 + 0.5 * (rho - 1.0), 1.0)
+    assert np.array_equal(got, want)
 
 
 @pytest.mark.parametrize("objective", ["threshold", "1f1b"])
