@@ -105,11 +105,12 @@ constexpr int kFinishThreads = 1024;
 // candidate and stage layout copied next to it, so that the host reads
 // everything with one copy.  Up to kSmall candidates (no partial minima), at most
 // kSmallSegment a configuration, a thread reads its configuration's records: one launch
-// instead of two, whose gap costs more than the reads.  us of the call, two launches ->
-// one, at 290, 2,048, 4,096 and 8,192 candidates: 6 a configuration 36.3 -> 31.9, 36.2 ->
-// 32.7, 36.1 -> 33.8; 16: 36.0 -> 33.6, 35.9 -> 33.7, 35.9 -> 34.3, 36.0 -> 36.0; 24: 36.1 ->
-// 35.5, 36.3 -> 35.5, 36.3 -> 35.9, 36.2 -> 36.7; 48: 36.1 -> 38.7, 36.2 -> 38.9.
-constexpr int64_t kSmall = 4096, kSmallSegment = 24;
+// instead of two, whose gap costs more than the reads, one after another, of records that
+// the stage DP has just written.  us of a whole planner call, two launches -> one: 2 a
+// configuration, 290 candidates 74.6 -> 71.5, 1,474: 81.6 -> 79.9; 4, 1,976: 80.5 -> 79.8, 2,948:
+// 82.1 -> 82.3; 6, 1,830: 85.6 -> 85.1, 2,964: 80.5 -> 81.2; 8, 1,160: 78.6 -> 77.2; 12, 1,740:
+// 80.4 -> 80.6; 16, 2,320: 78.5 -> 79.5; 18, 504: 76.5 -> 77.9.
+constexpr int64_t kSmall = 2048, kSmallSegment = 8;
 template <bool SMALL>
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const Best *__restrict__ partial, int64_t n_configs,
                                                            int64_t chunks, int64_t *__restrict__ config_best,

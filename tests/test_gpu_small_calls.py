@@ -53,21 +53,27 @@ def test_arg_min_around_the_one_launch_limit(planner, n, batch):
     check_arg_min(planner, 6, n, batch)
 
 
-@pytest.mark.parametrize("counts", [4, 5])   # 24 candidates a configuration, one launch up to 4,096; 30, two
-@pytest.mark.parametrize("n", [23, 25, 4095, 4096, 4097, 8000])
-def test_arg_min_of_long_segments(planner, counts, n):
+@pytest.mark.parametrize("orders,counts", [(2, 4), (2, 5), (6, 1), (6, 2)])   # one launch up to 8 a configuration
+@pytest.mark.parametrize("n", [7, 9, 2047, 2048, 2049, 4000])
+def test_arg_min_of_long_segments(planner, orders, counts, n):
     p = copy.deepcopy(planner.problem)
+    if orders == 2:   # two device types
+        c = p["cluster"]
+        c["n_types"] = 2
+        for f in ("count", "speed", "mem_bytes", "eff", "route_coef", "t_dense", "t_ffn"):
+            c[f] = c[f][:2]
+        c["bw"], c["alpha"], c["count"] = c["bw"][:2, :2], c["alpha"][:2, :2], np.array([32, 32], dtype=np.int32)
     p["space"]["micro"] = [8, 16, 32, 64, 128][:counts]
     pl = binding.Planner(p, "cuda:0")
     pl.run()
-    print(f"arg-min of {n} records, {6 * counts} a configuration", flush=True)
-    check_arg_min(pl, 6 * counts, n, 0)
+    print(f"arg-min of {n} records, {orders * counts} a configuration", flush=True)
+    check_arg_min(pl, orders * counts, n, 0)
 
 
-@pytest.mark.parametrize("layers,experts", [(32, 64), (33, 64), (33, 32), (32, 72), (8, 256), (127, 16), (9, 0)])
+@pytest.mark.parametrize("layers,experts", [(32, 64), (32, 72), (32, 80), (33, 64), (64, 32), (96, 16), (97, 16), (8, 256), (9, 0)])
 def test_load_imbalance_factors_of_either_kernel(planner, layers, experts):
-    """1 + gamma (rho - 1) of every layer, reduced by the cost-table workgroups (at most
-    eight counts a lane) or by a kernel before them."""
+    """1 + gamma (rho - 1) of every layer, reduced by the cost-table workgroups (up to
+    32 layers x 72 experts, 64 x 32, 96 x 16) or by a kernel before them."""
     e = max(experts, 1)
     p = workloads.random_tiny(40 + layers, n_layers=layers, n_types=2)
     rng = np.random.default_rng(layers * 1000 + experts)
