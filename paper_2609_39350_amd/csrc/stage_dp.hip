@@ -1610,7 +1610,11 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
         int64_t grid = (int64_t)ncu * (per_cu > 0 ? per_cu : 1);
         const bool few = n_keys <= 4 * grid;
         const bool brief = exact ? prune_window != 0 && n_layers * ppmax <= 1152 : ppmax <= 16 || n_micro <= 8;
+#ifdef HAPMOE_SECTION_CLOCKS   // every workgroup adds its clocks to one table: few workgroups
+        const bool each = n_keys <= grid && (few || brief);
+#else
         const bool each = (few || brief) && n_keys < int64_t(1) << 26;   // (2^32 threads: HIP's documented limit)
+#endif
         if (each || n_keys < grid) grid = n_keys;
         if (!each) hipLaunchKernelGGL(k_reset_queue, dim3(1), dim3(1), 0, s, queue);
         hipLaunchKernelGGL(each ? direct : queued, dim3((unsigned)grid), dim3(64), S.total, s, img, d_cand, L, tab,
