@@ -1597,7 +1597,7 @@ hipError_t launch_stage_dp(const void *d_image, const hapmoe_candidate *d_cand, 
     auto fit = [&](auto kern) { return hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 64, S.total); };
     auto go = [&](auto queued, auto direct) -> hipError_t {   // per_cu: the queued kernel's
         // One workgroup a key (the i-th takes the i-th largest) or resident workgroups that
-        // fetch keys off the queue.  The fetches are one chain of atomics, about 5 ns each, that
+        // fetch keys off the queue.  The fetches are one chain of atomics, about 13 ns each, that
         // short keys wait for; the dispatcher deals keys to the XCDs in turn whatever they take,
         // which costs where keys are long.  us a call, queue -> a workgroup a key: 32 layers,
         // 5,424 keys: 177 -> 116; 61 layers, 39,264: 634 -> 416; sequences, 118,440: 1,678 -> 789;

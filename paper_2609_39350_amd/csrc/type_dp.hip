@@ -38,11 +38,12 @@
 // a feasible path).  F and the back-trace pointers live in the workgroup's
 // slice of the workspace, end layers contiguous; the layer prefix sums, the
 // level lists and the incumbents in LDS.  Plain int64 min-plus work: no MFMA.
-// Bound by VALU issue inside the level rounds of the deepest keys (one
-// workgroup a CU, a 16-stage pass of 61 layers: 141 us before, 92 us now): so
-// split points run from the highest, where each next type allows a prefix of
-// them, and a sum carries its split point and type in its low bits.  804 keys,
-// PP <= 16: 12.0 -> 1.95 ms.
+// Bound by the waits of the level rounds (F from L2, a barrier a level) of the deepest
+// keys, one workgroup a CU: at 61 layers and 804 keys of up to 16 stages 76 % of the wave
+// cycles wait and VALU instructions take 15 % of the issue slots; a 16-stage pass takes
+// about 92 us (141 before split points ran from the highest, where each next type allows a
+// prefix of them, and a sum carried its split point and type in its low bits), and the
+// launch about as long as its longest key's passes.  12.0 -> 1.92 ms.
 #include <type_traits>
 
 #include "internal.h"

@@ -38,9 +38,11 @@
 // about 60 KB, two workgroups of eight waves a CU).  A key that needs more than tier 1
 // is given is left to a last tier of one workgroup a CU, with lists, intervals and
 // pointers in the workgroup's slice of the workspace.  61 layers, 31,296 keys, PP <=
-// 16: 33.0 -> 2.45 ms (one state a lane over the full rectangle, costs from global
-// memory and a one-lane back-trace before).  Running a window's split points from the
-// highest and leaving at the first above the threshold measured 4 % slower.
+// 16: the kernel 32.9 -> 2.36 ms (one state a lane over the full rectangle, costs from
+// global memory and a one-lane back-trace before); VALU instructions take 46 % of the
+// issue slots and 70 % of the wave cycles wait, for LDS and at the barrier of a level.
+// Running a window's split points from the highest and leaving at the first above the
+// threshold measured 4 % slower.
 #include "internal.h"
 
 namespace hapmoe {
