@@ -153,7 +153,7 @@ def leg_latency(torch, binding, workloads, dev, stream, cpu_sample):
     best plan beside it (the exact minimum can only be lower)."""
     import numpy as np
     out = {}
-    for n_config in (2, 3, 4):   # configuration 4: about 8 s a launch
+    for n_config in (2, 3, 4):
         p = workloads.config(n_config)
         pl = binding.Planner(p, dev)
         pl.eval_cost_tables()
@@ -176,6 +176,7 @@ def leg_latency(torch, binding, workloads, dev, stream, cpu_sample):
         rec = {"workload": f"config {n_config}: {WORKLOADS[n_config]}", "candidates": pl.n,
                "value": pl.n / elapsed, "unit": "candidates/s", "stage_dp_ms": ms,
                "feasible_candidates": int(ok.sum()),
+               # passes over ranges of the largest stage
                "thresholds_per_candidate": {"mean": float(st[ok, 0].mean()) if ok.any() else 0.0,
                                             "max": int(st[:, 0].max())},
                "relaxations_per_launch": relax,
@@ -279,7 +280,7 @@ def leg_free_types(torch, binding, workloads, dev, stream, steps, warmup, cpu_sa
         pf.eval_cost_tables()
         pf.stage_dp(stats=True)
         st = pf.stats()
-        # the 96-layer count DP runs about 2.4 s a launch: one timed launch after
+        # the 96-layer count DP runs 0.35 s a launch (1.4 s as 1F1B): one timed launch after
         # the statistics launch (which also warms it)
         k_steps, k_warm = (1, 0) if n_config == 4 and mode == 2 else (steps, warmup)
         plan, elapsed, dp_ms = _timed_steps(torch, pf, stream, k_steps, k_warm)

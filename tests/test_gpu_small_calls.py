@@ -53,8 +53,8 @@ def test_arg_min_around_the_one_launch_limit(planner, n, batch):
     check_arg_min(planner, 6, n, batch)
 
 
-@pytest.mark.parametrize("orders,counts", [(2, 4), (2, 5), (6, 1), (6, 2)])   # one launch up to 8 a configuration
-@pytest.mark.parametrize("n", [7, 9, 2047, 2048, 2049, 4000])
+@pytest.mark.parametrize("orders,counts", [(2, 8), (2, 9), (6, 2), (6, 3)])   # one launch up to 16 a configuration
+@pytest.mark.parametrize("n", [11, 13, 2047, 2048, 2049, 4000])
 def test_arg_min_of_long_segments(planner, orders, counts, n):
     p = copy.deepcopy(planner.problem)
     if orders == 2:   # two device types
@@ -63,7 +63,7 @@ def test_arg_min_of_long_segments(planner, orders, counts, n):
         for f in ("count", "speed", "mem_bytes", "eff", "route_coef", "t_dense", "t_ffn"):
             c[f] = c[f][:2]
         c["bw"], c["alpha"], c["count"] = c["bw"][:2, :2], c["alpha"][:2, :2], np.array([32, 32], dtype=np.int32)
-    p["space"]["micro"] = [8, 16, 32, 64, 128][:counts]
+    p["space"]["micro"] = [8, 16, 32, 64, 128, 5, 6, 7, 9][:counts]
     pl = binding.Planner(p, "cuda:0")
     pl.run()
     print(f"arg-min of {n} records, {orders * counts} a configuration", flush=True)
