@@ -109,9 +109,9 @@ constexpr int kFinishThreads = 1024;
 // the stage DP has just written.  us of a whole planner call, two launches -> one: 2 a
 // configuration, 290 candidates 74.6 -> 71.5, 1,474: 81.6 -> 79.9; 4, 1,976: 80.5 -> 79.8, 2,948:
 // 82.1 -> 82.3; 6, 1,830: 85.6 -> 85.1, 2,964: 80.5 -> 81.2; 8, 1,160: 78.6 -> 77.2; 12, 1,740:
-// 80.4 -> 80.6; 16, 2,320: 78.5 -> 79.5; 18, 504: 76.5 -> 77.9.  A planner built anew for 12 to
-// 16 a configuration behind the load-imbalance kernel (2,032 candidates): 195 -> 163, as a wait
-// of more than some 60 us sleeps and wakes late.
+// 80.4 -> 80.6; 16, 2,320: 78.5 -> 79.5; 18, 504: 76.5 -> 77.9.  A planner built anew takes 28 us
+// more with a fifth launch (behind the load-imbalance kernel, 16 a configuration, 2,032
+// candidates: 195 -> 163).
 constexpr int64_t kSmall = 2048, kSmallSegment = 16;
 template <bool SMALL>
 __global__ __launch_bounds__(kFinishThreads) void k_finish(const Best *__restrict__ partial, int64_t n_configs,

@@ -581,23 +581,23 @@ __global__ __launch_bounds__(kThreads, 8) void k_cost_tables(const unsigned char
 
 namespace hapmoe {
 
-// Every workgroup of k_cost_tables reduces the router counts itself, eight lanes a layer
-// and 32 layers a round, while that takes at most kOwnSkew steps (a round's counts a lane,
-// and one): it then costs less than the launch before it.  us of the tables' call, two
-// kernels -> one, with 145, 904 and 1,454 to 2,350 configurations: 8 layers x 64 experts (9
-// steps) 33.2 -> 30.8, 39.0 -> 36.8, 45.7 -> 43.5; 32 x 64 (9) 32.5 -> 30.8, 38.9 -> 37.4, 69.4 ->
-// 68.4; 61 x 32 (10) 33.9 -> 31.9, 40.0 -> 38.7, 46.9 -> 46.4; 96 x 16 (9) 34.1 -> 32.4, 40.7 ->
-// 40.3, 47.6 -> 47.5; 127 x 16 (12) 34.2 -> 33.3, 41.3 -> 41.8, 48.2 -> 49.4; 32 x 128 (17) 32.9 ->
-// 31.9, 39.5 -> 38.8, 69.4 -> 71.0; 33 x 64 (18) 32.4 -> 31.8, 39.1 -> 38.6, 69.0 -> 70.6; 8 x 256
-// (33) 32.3 -> 32.7, 38.6 -> 39.3, 47.5 -> 48.2.
-constexpr int kOwnSkew = 10;
+// Up to kOwnSkew router counts (16 KB) every workgroup of k_cost_tables reduces them
+// itself, eight lanes a layer and 32 layers a round, instead of a launch before it.  us of
+// the tables' call, two kernels -> one, with 145, 904 and 1,454 to 2,350 configurations: 8
+// layers x 64 experts 33.2 -> 30.8, 39.0 -> 36.8, 45.7 -> 43.5; 32 x 64: 32.5 -> 30.8, 38.9 ->
+// 37.4, 69.4 -> 68.4; 61 x 32: 33.9 -> 31.9, 40.0 -> 38.7, 46.9 -> 46.4; 33 x 64 (2,112 counts,
+// a second round): 32.4 -> 31.8, 39.1 -> 38.6, 69.0 -> 70.6; 32 x 128: 32.9 -> 31.9, 39.5 ->
+// 38.8, 69.4 -> 71.0; 61 x 256: 36.1 -> 40.0, 42.9 -> 48.7, 73.3 -> 92.7.  Many counts a lane
+// or many rounds cost a little below the limit too (8 x 256: 38.6 -> 39.3, 127 x 16: 41.3 ->
+// 41.8), but a fifth launch costs a planner built anew 28 us (8 x 256: 157 -> 185 us).
+constexpr int64_t kOwnSkew = 2048;
 
 hipError_t launch_cost_tables(const void *d_image, const hapmoe_candidate *d_cand, int64_t per_config,
                               int n_layers, int n_experts, const TablesLayout &L, int64_t cfg_lo, int64_t n_cfg, void *d_tables,
                               double *d_debug, const DebugLayout &D, hipStream_t s)
 {
     if (n_cfg <= 0) return hipSuccess;
-    const bool own_skew = (n_layers + 31) / 32 * ((n_experts + 7) / 8 + 1) <= kOwnSkew;
+    const bool own_skew = (int64_t)n_layers * n_experts <= kOwnSkew;
     if (!own_skew)
         hipLaunchKernelGGL(k_layer_skew, dim3((unsigned)n_layers), dim3(kThreads), 0, s,
                            static_cast<const unsigned char *>(d_image), L, static_cast<unsigned char *>(d_tables));
